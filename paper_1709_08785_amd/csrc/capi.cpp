@@ -1164,13 +1164,13 @@ extern "C" int wc_link_grad(wc_lattice *lat, const void *lam_dev, const void *x_
     if (!lat->have_links) return wc_fail(WC_ENOTREADY, "wc_link_grad before wc_load_links");
     if (!(kappa >= 0.0) || !(csw >= 0.0)) return wc_fail(WC_EINVAL, "need kappa >= 0 and csw >= 0");
     const size_t sb = spinor_bytes(P64, lat->Vh);
-    void *lam, *x, *N = nullptr;
+    void *lam, *x, *X = nullptr;
     if (int rc = lwork(lat, LW_GLAM, 2 * sb, &lam)) return rc;
     if (int rc = lwork(lat, LW_GX, 2 * sb, &x)) return rc;
     const bool clover = include_clover && csw != 0.0;
     if (clover)
-        if (int rc = lwork(lat, LW_GN, (size_t)6 * 2 * 9 * 16 * lat->Vh, &N)) return rc;
+        if (int rc = lwork(lat, LW_GCLOV, grad_x_bytes(lat), &X)) return rc;
     if (int rc = launch_pack_spinor(lat, P64, lam, lam_dev)) return rc;
     if (int rc = launch_pack_spinor(lat, P64, x, x_dev)) return rc;
-    return launch_link_grad(lat, lam, x, gradU_dev, N, kappa, csw, clover);
+    return launch_link_grad(lat, lam, x, gradU_dev, X, kappa, csw, clover);
 }

@@ -14,9 +14,17 @@
 //     (kappa c_SW / 8) (B N^T A)^dagger (or B N^T A when the factor is daggered),
 //     A = f1..f_{k-1}, B = f_{k+1}..f4.
 //
-// The clover part is a gather: one thread per link visits the 8 leaf slots of
-// each of the 3 planes that contain it, so no two threads write the same
-// link and the result is deterministic.
+// Summed over the four leaf sites of a plaquette the clover part closes into
+// staples with X = N^T inserted at the corners.  For link d at m, other
+// direction e, and the path a b c from m+d back to m around the plaquette,
+//   S = X(m+d) a b c + a X(.) b c + a b X(.) c + a b c X(m)
+//     = ((X1 a + a X2) b + (a b) X3) c + (a b c) X0,
+// and the link receives +-(S_up - S_down)^dagger, + for d < e: where the
+// plaquette holds the link daggered, its term is S taken with X^dagger in
+// place of X, and X^dagger = -X.
+//
+// The clover part is a gather: one thread per link visits its 6 plaquettes,
+// so no two threads write the same link and the result is deterministic.
 #include "reduce.hpp"
 
 namespace {
@@ -24,17 +32,75 @@ namespace {
 using C = cx<double>;
 using M3 = Mat3<double>;
 
-__device__ __forceinline__ M3 mmul(const M3 &a, const M3 &b) {
-    M3 c;
+// X (N^T of a site and plane) is anti-Hermitian: its imaginary diagonal and the
+// entries above the diagonal, 9 reals
+struct AntiHerm {
+    double d[3];
+    C o[3];  // (0,1) (0,2) (1,2)
+};
+
+// entry (i, j), i != j
+__device__ __forceinline__ C ah_off(const AntiHerm &x, int i, int j) {
+    const C v = x.o[i + j - 1];
+    return i < j ? v : C{-v.re, v.im};
+}
+
+// c += a b
+__device__ __forceinline__ void mmac(M3 &c, const M3 &a, const M3 &b) {
 #pragma unroll
     for (int i = 0; i < 3; i++)
 #pragma unroll
-        for (int j = 0; j < 3; j++) {
-            C s = {0, 0};
+        for (int j = 0; j < 3; j++)
 #pragma unroll
-            for (int k = 0; k < 3; k++) cmac(s, a.m[3 * i + k], b.m[3 * k + j]);
-            c.m[3 * i + j] = s;
-        }
+            for (int k = 0; k < 3; k++) cmac(c.m[3 * i + j], a.m[3 * i + k], b.m[3 * k + j]);
+}
+// c += a b^dagger
+__device__ __forceinline__ void mmac_d(M3 &c, const M3 &a, const M3 &b) {
+#pragma unroll
+    for (int i = 0; i < 3; i++)
+#pragma unroll
+        for (int j = 0; j < 3; j++)
+#pragma unroll
+            for (int k = 0; k < 3; k++) cmacc(c.m[3 * i + j], b.m[3 * j + k], a.m[3 * i + k]);
+}
+// c += x a
+__device__ __forceinline__ void xmac(M3 &c, const AntiHerm &x, const M3 &a) {
+#pragma unroll
+    for (int i = 0; i < 3; i++)
+#pragma unroll
+        for (int j = 0; j < 3; j++)
+#pragma unroll
+            for (int k = 0; k < 3; k++) {
+                C &t = c.m[3 * i + j];
+                if (k == i) {
+                    t.re = fmar(-x.d[i], a.m[3 * k + j].im, t.re);
+                    t.im = fmar(x.d[i], a.m[3 * k + j].re, t.im);
+                } else {
+                    cmac(t, ah_off(x, i, k), a.m[3 * k + j]);
+                }
+            }
+}
+// c += a x
+__device__ __forceinline__ void macx(M3 &c, const M3 &a, const AntiHerm &x) {
+#pragma unroll
+    for (int i = 0; i < 3; i++)
+#pragma unroll
+        for (int j = 0; j < 3; j++)
+#pragma unroll
+            for (int k = 0; k < 3; k++) {
+                C &t = c.m[3 * i + j];
+                if (k == j) {
+                    t.re = fmar(-x.d[j], a.m[3 * i + k].im, t.re);
+                    t.im = fmar(x.d[j], a.m[3 * i + k].re, t.im);
+                } else {
+                    cmac(t, a.m[3 * i + k], ah_off(x, k, j));
+                }
+            }
+}
+__device__ __forceinline__ M3 mzero() {
+    M3 c;
+#pragma unroll
+    for (int k = 0; k < 9; k++) c.m[k] = {0.0, 0.0};
     return c;
 }
 __device__ __forceinline__ M3 mdag(const M3 &a) {
@@ -43,20 +109,6 @@ __device__ __forceinline__ M3 mdag(const M3 &a) {
     for (int i = 0; i < 3; i++)
 #pragma unroll
         for (int j = 0; j < 3; j++) c.m[3 * i + j] = conjx(a.m[3 * j + i]);
-    return c;
-}
-__device__ __forceinline__ M3 mtrans(const M3 &a) {
-    M3 c;
-#pragma unroll
-    for (int i = 0; i < 3; i++)
-#pragma unroll
-        for (int j = 0; j < 3; j++) c.m[3 * i + j] = a.m[3 * j + i];
-    return c;
-}
-__device__ __forceinline__ M3 meye() {
-    M3 c;
-#pragma unroll
-    for (int k = 0; k < 9; k++) c.m[k] = {(k % 4 == 0) ? 1.0 : 0.0, 0.0};
     return c;
 }
 
@@ -113,50 +165,28 @@ __device__ __forceinline__ int plane_of(int mu, int nu) {
     return mu == 0 ? nu - 1 : (mu == 1 ? nu + 1 : 5);
 }
 
-// canonical gradient slot of link (mu, site n) -> 9 complex128
-__device__ __forceinline__ double2 *gslot(double2 *G, const Geom &g, int mu, const SiteCoord &c) {
-    const size_t n = (size_t)c.x + (size_t)g.L[0] * c.row;
-    return G + ((size_t)mu * 2 * g.Vh + n) * 9;
+// X_{mu nu}(n) = (M - M^dagger)^T for the 6 planes: per (plane, parity) a slab of
+// 64-site tiles, the 9 reals of AntiHerm plane after plane
+constexpr int kXSite = 9 * 8;  // bytes per site
+__host__ __device__ inline size_t x_slab_bytes(int Vh) { return (size_t)pad_sites(Vh) * kXSite; }
+
+__device__ __forceinline__ AntiHerm load_x(const char *slab, int i) {
+    AntiHerm x;
+#pragma unroll
+    for (int k = 0; k < 3; k++) x.d[k] = *tp<double, kXSite>(slab, i, 8 * k);
+#pragma unroll
+    for (int k = 0; k < 3; k++)
+        x.o[k] = {*tp<double, kXSite>(slab, i, 24 + 16 * k), *tp<double, kXSite>(slab, i, 32 + 16 * k)};
+    return x;
 }
 
-// hopping part; overwrites G
-__global__ __launch_bounds__(kBlock) void k_grad_hop(Geom g, const char *lam, const char *x, size_t sb, double2 *G,
-                                                     double kappa) {
-    const int i = blockIdx.x * kBlock + threadIdx.x;
-    const int slab = blockIdx.y;  // 2 mu + parity
-    if (i >= g.Vh) return;
-    const int mu = slab >> 1, par = slab & 1;
-    const SiteCoord c = eo_coords(g, i, par);
-    const int np = eo_neighbour(g, c, mu, +1);
-    const Spinor<double> lm = SpinorIO<P64>::load(lam + par * sb, g.Vh, i);
-    const Spinor<double> lp = SpinorIO<P64>::load(lam + (1 - par) * sb, g.Vh, np);
-    const Spinor<double> xm = SpinorIO<P64>::load(x + par * sb, g.Vh, i);
-    const Spinor<double> xp = SpinorIO<P64>::load(x + (1 - par) * sb, g.Vh, np);
-    Spinor<double> y, z;
-    one_minus_gamma(mu, true, xp, y);
-    one_minus_gamma(mu, false, xm, z);
-    double2 *out = gslot(G, g, mu, c);
-#pragma unroll
-    for (int a = 0; a < 3; a++)
-#pragma unroll
-        for (int b = 0; b < 3; b++) {
-            C s = {0, 0};
-#pragma unroll
-            for (int al = 0; al < 4; al++) {
-                cmac(s, lm.c[3 * al + a], conjx(y.c[3 * al + b]));
-                cmac(s, z.c[3 * al + a], conjx(lp.c[3 * al + b]));
-            }
-            out[3 * a + b] = make_double2(kappa * s.re, kappa * s.im);
-        }
-}
-
-// N_{mu nu}(n) = M - M^dagger for the 6 planes, FP64 [plane][parity][9][Vh] double2
-__global__ __launch_bounds__(kBlock) void k_grad_N(Geom g, const char *lam, const char *x, size_t sb, double2 *N) {
+__global__ __launch_bounds__(kBlock) void k_grad_X(Geom g, const char *lam, const char *x, size_t sb, char *X) {
     const int i = blockIdx.x * kBlock + threadIdx.x;
     const int par = blockIdx.y;
     if (i >= g.Vh) return;
     const Spinor<double> l = SpinorIO<P64>::load(lam + par * sb, g.Vh, i);
     const Spinor<double> xv = SpinorIO<P64>::load(x + par * sb, g.Vh, i);
+#pragma unroll
     for (int p = 0; p < 6; p++) {
         Spinor<double> y;
         gamma_pair(p, xv, y);
@@ -170,106 +200,157 @@ __global__ __launch_bounds__(kBlock) void k_grad_N(Geom g, const char *lam, cons
                 for (int al = 0; al < 4; al++) cmacc(s, l.c[3 * al + a], y.c[3 * al + b]);
                 M[3 * a + b] = s;
             }
-        double2 *o = N + (size_t)(2 * p + par) * 9 * g.Vh;
+        char *slab = X + (size_t)(2 * p + par) * x_slab_bytes(g.Vh);
 #pragma unroll
-        for (int a = 0; a < 3; a++)
+        for (int k = 0; k < 3; k++) *tp<double, kXSite>(slab, i, 8 * k) = 2.0 * M[4 * k].im;
 #pragma unroll
-            for (int b = 0; b < 3; b++) {
-                const C v = M[3 * a + b] - conjx(M[3 * b + a]);
-                o[(size_t)(3 * a + b) * g.Vh + i] = make_double2(v.re, v.im);
-            }
+        for (int k = 0; k < 3; k++) {
+            const int a = k == 2 ? 1 : 0, b = k == 0 ? 1 : 2;  // (0,1) (0,2) (1,2)
+            const C v = M[3 * b + a] - conjx(M[3 * a + b]);
+            *tp<double, kXSite>(slab, i, 24 + 16 * k) = v.re;
+            *tp<double, kXSite>(slab, i, 32 + 16 * k) = v.im;
+        }
     }
 }
 
-// the four counter-clockwise leaves of Q_{mu nu}(n), factor by factor:
-// {0: mu-link / 1: nu-link, root offset along mu, root offset along nu, daggered}
-__constant__ int kLeafG[4][4][4] = {
-    // U_mu(n) U_nu(n+mu) U_mu(n+nu)^dag U_nu(n)^dag
-    {{0, 0, 0, 0}, {1, 1, 0, 0}, {0, 0, 1, 1}, {1, 0, 0, 1}},
-    // U_nu(n) U_mu(n+nu-mu)^dag U_nu(n-mu)^dag U_mu(n-mu)
-    {{1, 0, 0, 0}, {0, -1, 1, 1}, {1, -1, 0, 1}, {0, -1, 0, 0}},
-    // U_mu(n-mu)^dag U_nu(n-mu-nu)^dag U_mu(n-mu-nu) U_nu(n-nu)
-    {{0, -1, 0, 1}, {1, -1, -1, 1}, {0, -1, -1, 0}, {1, 0, -1, 0}},
-    // U_nu(n-nu)^dag U_mu(n-nu) U_nu(n+mu-nu) U_mu(n)^dag
-    {{1, 0, -1, 1}, {0, 0, -1, 0}, {1, 1, -1, 0}, {0, 0, 0, 1}},
-};
+// h += sum over spin of a b^dagger
+__device__ __forceinline__ void outer_mac(M3 &h, const Spinor<double> &a, const Spinor<double> &b) {
+#pragma unroll
+    for (int i = 0; i < 3; i++)
+#pragma unroll
+        for (int j = 0; j < 3; j++)
+#pragma unroll
+            for (int al = 0; al < 4; al++) cmacc(h.m[3 * i + j], b.c[3 * al + j], a.c[3 * al + i]);
+}
 
-// clover part; adds into G
-__global__ __launch_bounds__(64) void k_grad_clover(Geom g, const double2 *l64, const double2 *N, double2 *G,
-                                                    double fac) {
-    const int i = blockIdx.x * 64 + threadIdx.x;
-    const int slab = blockIdx.y;  // 2 d + parity
-    if (i >= g.Vh) return;
-    const int d = slab >> 1, par = slab & 1;
-    const SiteCoord c = eo_coords(g, i, par);
-    const int cm[4] = {c.x, c.y, c.z, c.t};
-    M3 acc;
+// lexicographic step of one site along a direction, with the periodic wrap
+__device__ __forceinline__ int lex_step(const Geom &g, const SiteCoord &c, int mu, bool up) {
+    const int x = mu == 0 ? c.x : mu == 1 ? c.y : mu == 2 ? c.z : c.t;
+    const int stride = mu == 0 ? 1 : mu == 1 ? g.L[0] : mu == 2 ? g.L[0] * g.L[1] : g.L[0] * g.L[1] * g.L[2];
+    const int L = g.L[mu];
+    if (up) return x == L - 1 ? -(L - 1) * stride : stride;
+    return x == 0 ? (L - 1) * stride : -stride;
+}
+
+// The gradient of a tile of 64 sites of one parity, one wavefront per link
+// direction.  The clover part sums 6 plaquettes of 8 matrix products each, the
+// hopping part is added, and the link is written once.
+//
+// What bounds it: with the clover part, FP64 arithmetic (48 products of 3x3
+// matrices, about 10 kflop a link) and the loads that feed it, 3.9 KB a link
+// through the caches; the four directions of a tile sit in one workgroup so
+// that they find each other's links and X in L1.  The links leave through LDS:
+// a lane's 9 entries are 144 bytes at a stride of 288 (the other parity's sites
+// lie between), which as lane-wise stores touches 64 lines per instruction.
+template <bool CLOVER>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) void k_grad(
+    Geom g, const char *lam, const char *x, size_t sb, const double2 *l64, const char *X, double2 *G, double kappa,
+    double fac) {
+    __shared__ double2 sh[kWaves][64 * 9];
+    const int lb = xcd_block(blockIdx.x, gridDim.x, 64);  // both parities of a tile run on one XCD
+    const int tile = lb >> 1, par = lb & 1;
+    const int d = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+    const int i = tile * 64 + lane;
+    const int live = min(64, g.Vh - tile * 64);
+    if (lane < live) {
+        const SiteCoord c = eo_coords(g, i, par);
+        const int n = c.x + g.L[0] * c.row;
+        const int sd = lex_step(g, c, d, true);
+        const int nd = (n + sd) >> 1;
+        M3 acc = mzero();
+        if (CLOVER) {
+            const size_t ls = link_slab_bytes(P64, g.Vh);
+            const char *L = (const char *)l64;
+            M3 sum = mzero();
+#pragma unroll 1
+            for (int k = 0; k < 6; k++) {
+                const int e = (k >> 1) + ((k >> 1) >= d ? 1 : 0);
+                const bool up = !(k & 1);
+                const int se = lex_step(g, c, e, up);
+                const int ne = (n + se) >> 1, nde = (n + sd + se) >> 1;
+                const int mu = min(d, e), nu = max(d, e);
+                const char *xs0 = X + (size_t)(2 * plane_of(mu, nu) + par) * x_slab_bytes(g.Vh);
+                const char *xs1 = X + (size_t)(2 * plane_of(mu, nu) + 1 - par) * x_slab_bytes(g.Vh);
+                // path m+d -> m+d+-e -> m+-e -> m: the e link beside m+d, the d
+                // link across (always daggered) and the e link beside m
+                const Mat3<double> ue = LinkIO<P64>::load<false>(L + (size_t)(2 * e + (up ? 1 - par : par)) * ls, g.Vh,
+                                                                 up ? nd : nde);
+                const M3 a = up ? ue : mdag(ue);
+                M3 q = mzero();
+                xmac(q, load_x(xs1, nd), a);
+                macx(q, a, load_x(xs0, nde));
+                const Mat3<double> ud = LinkIO<P64>::load<false>(L + (size_t)(2 * d + 1 - par) * ls, g.Vh, ne);
+                M3 r = mzero(), q2 = mzero();
+                mmac_d(r, a, ud);
+                mmac_d(q2, q, ud);
+                macx(q2, r, load_x(xs1, ne));
+                const Mat3<double> uc = LinkIO<P64>::load<false>(L + (size_t)(2 * e + (up ? par : 1 - par)) * ls, g.Vh,
+                                                                 up ? i : ne);
+                const M3 cc = up ? mdag(uc) : uc;
+                M3 rc = mzero(), s = mzero();
+                mmac(rc, r, cc);
+                mmac(s, q2, cc);
+                macx(s, rc, load_x(xs0, i));
+                const double sg = ((d < e) == up) ? 1.0 : -1.0;
 #pragma unroll
-    for (int k = 0; k < 9; k++) acc.m[k] = {0, 0};
-    for (int e = 0; e < 4; e++) {
-        if (e == d) continue;
-        const int mu = d < e ? d : e, nu = d < e ? e : d;
-        const int role = (d == mu) ? 0 : 1;
-        const int p = plane_of(mu, nu);
-        for (int lf = 0; lf < 4; lf++) {
-            for (int k = 0; k < 4; k++) {
-                if (kLeafG[lf][k][0] != role) continue;
-                // leaf site n = m - offset of factor k
-                int n[4] = {cm[0], cm[1], cm[2], cm[3]};
-                n[mu] -= kLeafG[lf][k][1];
-                n[nu] -= kLeafG[lf][k][2];
-                M3 A = meye(), B = meye();
-                for (int j = 0; j < 4; j++) {
-                    if (j == k) continue;
-                    int s[4] = {n[0], n[1], n[2], n[3]};
-                    s[mu] += kLeafG[lf][j][1];
-                    s[nu] += kLeafG[lf][j][2];
-                    const int dir = kLeafG[lf][j][0] ? nu : mu;
-                    M3 f = link64(l64, g, dir, site_ref(g, s[0], s[1], s[2], s[3]));
-                    if (kLeafG[lf][j][3]) f = mdag(f);
-                    if (j < k) A = mmul(A, f);
-                    else B = mmul(B, f);
-                }
-                const SiteRef sn = site_ref(g, n[0], n[1], n[2], n[3]);
-                M3 Nm;
-                const double2 *np_ = N + (size_t)(2 * p + sn.par) * 9 * g.Vh;
-#pragma unroll
-                for (int q = 0; q < 9; q++) {
-                    const double2 v = np_[(size_t)q * g.Vh + sn.i];
-                    Nm.m[q] = {v.x, v.y};
-                }
-                const M3 P = mmul(mmul(B, mtrans(Nm)), A);
-                const M3 add = kLeafG[lf][k][3] ? P : mdag(P);
-#pragma unroll
-                for (int q = 0; q < 9; q++) acc.m[q] = acc.m[q] + add.m[q];
+                for (int j = 0; j < 9; j++) sum.m[j] = sum.m[j] + sg * s.m[j];
             }
-        }
-    }
-    double2 *out = gslot(G, g, d, c);
 #pragma unroll
-    for (int q = 0; q < 9; q++) {
-        const double2 v = out[q];
-        out[q] = make_double2(v.x + fac * acc.m[q].re, v.y + fac * acc.m[q].im);
+            for (int a = 0; a < 3; a++)
+#pragma unroll
+                for (int b = 0; b < 3; b++) acc.m[3 * a + b] = fac * conjx(sum.m[3 * b + a]);
+        }
+        {
+            // kappa [lam(m) ((1 - g_d) x(m+d))^dag + ((1 + g_d) x(m)) lam(m+d)^dag]
+            M3 h = mzero();
+            Spinor<double> y;
+            {
+                const Spinor<double> lm = SpinorIO<P64>::load(lam + par * sb, g.Vh, i);
+                one_minus_gamma(d, true, SpinorIO<P64>::load(x + (1 - par) * sb, g.Vh, nd), y);
+                outer_mac(h, lm, y);
+            }
+            {
+                const Spinor<double> lp = SpinorIO<P64>::load(lam + (1 - par) * sb, g.Vh, nd);
+                one_minus_gamma(d, false, SpinorIO<P64>::load(x + par * sb, g.Vh, i), y);
+                outer_mac(h, y, lp);
+            }
+#pragma unroll
+            for (int k = 0; k < 9; k++) acc.m[k] = acc.m[k] + kappa * h.m[k];
+        }
+#pragma unroll
+        for (int k = 0; k < 9; k++) sh[d][lane * 9 + k] = make_double2(acc.m[k].re, acc.m[k].im);
+    }
+    __syncthreads();
+    double2 *out = G + (size_t)d * 2 * g.Vh * 9;
+    for (int k = lane; k < live * 9; k += 64) {
+        const int s = k / 9;
+        const SiteCoord c = eo_coords(g, tile * 64 + s, par);
+        out[(size_t)(c.x + g.L[0] * c.row) * 9 + (k - 9 * s)] = sh[d][k];
     }
 }
 
 }  // namespace
 
-int launch_link_grad(wc_lattice *lat, const void *lam_eo, const void *x_eo, void *G, void *Nbuf, double kappa,
+size_t grad_x_bytes(const wc_lattice *lat) { return 12 * x_slab_bytes(lat->Vh); }
+
+int launch_link_grad(wc_lattice *lat, const void *lam_eo, const void *x_eo, void *G, void *Xbuf, double kappa,
                      double csw, bool clover) {
     const size_t sb = spinor_bytes(P64, lat->Vh);
-    dim3 grid((lat->Vh + kBlock - 1) / kBlock, 8);
-    hipLaunchKernelGGL(k_grad_hop, grid, dim3(kBlock), 0, lat->stream, lat->g, (const char *)lam_eo,
-                       (const char *)x_eo, sb, (double2 *)G, kappa);
+    const dim3 grid(2 * (pad_sites(lat->Vh) / 64));
+    if (!clover) {
+        hipLaunchKernelGGL(k_grad<false>, grid, dim3(kBlock), 0, lat->stream, lat->g, (const char *)lam_eo,
+                           (const char *)x_eo, sb, (const double2 *)lat->links[P64], (const char *)nullptr,
+                           (double2 *)G, kappa, 0.0);
+        WC_HIP(hipGetLastError());
+        return WC_OK;
+    }
+    dim3 gridX((lat->Vh + kBlock - 1) / kBlock, 2);
+    hipLaunchKernelGGL(k_grad_X, gridX, dim3(kBlock), 0, lat->stream, lat->g, (const char *)lam_eo,
+                       (const char *)x_eo, sb, (char *)Xbuf);
     WC_HIP(hipGetLastError());
-    if (!clover) return WC_OK;
-    dim3 gridN((lat->Vh + kBlock - 1) / kBlock, 2);
-    hipLaunchKernelGGL(k_grad_N, gridN, dim3(kBlock), 0, lat->stream, lat->g, (const char *)lam_eo,
-                       (const char *)x_eo, sb, (double2 *)Nbuf);
-    WC_HIP(hipGetLastError());
-    dim3 gridC((lat->Vh + 63) / 64, 8);
-    hipLaunchKernelGGL(k_grad_clover, gridC, dim3(64), 0, lat->stream, lat->g, (const double2 *)lat->links[P64],
-                       (const double2 *)Nbuf, (double2 *)G, kappa * csw / 8.0);
+    hipLaunchKernelGGL(k_grad<true>, grid, dim3(kBlock), 0, lat->stream, lat->g, (const char *)lam_eo,
+                       (const char *)x_eo, sb, (const double2 *)lat->links[P64], (const char *)Xbuf, (double2 *)G,
+                       kappa, kappa * csw / 8.0);
     WC_HIP(hipGetLastError());
     return WC_OK;
 }

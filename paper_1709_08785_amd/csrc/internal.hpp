@@ -152,7 +152,7 @@ struct BatchCache {
 };
 
 // lattice-owned scratch buffers (operator applications, gradients)
-enum LatWorkId { LW_APPLY_IN = 0, LW_APPLY_OUT, LW_APPLY_TMP, LW_GLAM, LW_GX, LW_GN, LW_COUNT };
+enum LatWorkId { LW_APPLY_IN = 0, LW_APPLY_OUT, LW_APPLY_TMP, LW_GLAM, LW_GX, LW_GCLOV, LW_COUNT };
 
 struct wc_lattice {
     // process-unique number of this handle (never reused, unlike its address):
@@ -468,7 +468,9 @@ int launch_links_full32(wc_lattice *lat);  // links18 from the FP64 copy
 // builds F and F^-1; *bad_blocks (device word, zeroed by the caller) receives the
 // number of 6x6 blocks that are not positive definite
 int launch_build_clover(wc_lattice *lat, double kappa, double csw, unsigned *bad_blocks);
-int launch_link_grad(wc_lattice *lat, const void *lam_eo, const void *x_eo, void *G, void *Nbuf, double kappa,
+// Xbuf: grad_x_bytes() of scratch for the clover part
+size_t grad_x_bytes(const wc_lattice *lat);
+int launch_link_grad(wc_lattice *lat, const void *lam_eo, const void *x_eo, void *G, void *Xbuf, double kappa,
                      double csw, bool clover);
 
 // solver entry used by wc_solve and the batched solves (solver.cpp)
