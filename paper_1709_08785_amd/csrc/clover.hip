@@ -13,191 +13,122 @@
 // as A - B and on the g5 = -1 space (u, u) as A + B.  Stored per site are
 // M1 = (A - B)/2 and M2 = (A + B)/2 (and the same for the inverses), which
 // is what the Dirac-basis epilogue of the stencil consumes.
+//
+// What bounds it: the six stored copies (2024 B a site) and the FP64 products
+// (60 of 3x3 matrices a site).  At 24^3x48 it takes 634 us, 2.1 TB/s of stores;
+// one thread per site with indexed 6x6 arrays in scratch took 5095 us.
+//
+// One workgroup builds the 64 sites of a tile.  Six wavefronts, one per plane,
+// first leave Fhat of their plane in LDS; four of them then each produce one of
+// the four stored blocks (F and F^-1 of either chirality).  Everything lives in
+// registers: the products are unrolled, and a block is inverted in place as its
+// 36 packed reals.
+#include "mat3.hpp"
 #include "reduce.hpp"
 
 namespace {
 
-using C = cx<double>;
-
-struct M3 {
-    C m[9];
-};
-
-__device__ __forceinline__ M3 m3mul(const M3 &a, const M3 &b) {
-    M3 c;
-#pragma unroll
-    for (int i = 0; i < 3; i++)
-#pragma unroll
-        for (int j = 0; j < 3; j++) {
-            C s = {0, 0};
-#pragma unroll
-            for (int k = 0; k < 3; k++) cmac(s, a.m[3 * i + k], b.m[3 * k + j]);
-            c.m[3 * i + j] = s;
-        }
-    return c;
-}
-
-// a * b^dagger
-__device__ __forceinline__ M3 m3mul_d(const M3 &a, const M3 &b) {
-    M3 c;
-#pragma unroll
-    for (int i = 0; i < 3; i++)
-#pragma unroll
-        for (int j = 0; j < 3; j++) {
-            C s = {0, 0};
-#pragma unroll
-            for (int k = 0; k < 3; k++) cmac(s, a.m[3 * i + k], conjx(b.m[3 * j + k]));
-            c.m[3 * i + j] = s;
-        }
-    return c;
-}
-
-// a^dagger * b
-__device__ __forceinline__ M3 m3dmul(const M3 &a, const M3 &b) {
-    M3 c;
-#pragma unroll
-    for (int i = 0; i < 3; i++)
-#pragma unroll
-        for (int j = 0; j < 3; j++) {
-            C s = {0, 0};
-#pragma unroll
-            for (int k = 0; k < 3; k++) cmac(s, conjx(a.m[3 * k + i]), b.m[3 * k + j]);
-            c.m[3 * i + j] = s;
-        }
-    return c;
-}
-
-struct LinkView {
-    Geom g;
-    const double2 *l64;  // tiled FP64 link slabs [mu][parity]
-
-    __device__ M3 at(int mu, int x, int y, int z, int t) const {
-        const int L0 = g.L[0], L1 = g.L[1], L2 = g.L[2], L3 = g.L[3];
-        x = (x + L0) % L0;
-        y = (y + L1) % L1;
-        z = (z + L2) % L2;
-        t = (t + L3) % L3;
-        const int par = (x + y + z + t) & 1;
-        const int n = x + L0 * (y + L1 * (z + L2 * t));
-        const int i = n >> 1;
-        const char *slab = (const char *)l64 + (size_t)(2 * mu + par) * link_slab_bytes(P64, g.Vh);
-        M3 u;
-#pragma unroll
-        for (int k = 0; k < 9; k++) {
-            double2 v = *tp<double2, 144>(slab, i, 16 * k);
-            u.m[k] = {v.x, v.y};
-        }
-        return u;
-    }
-};
-
-// Fhat_{mu nu}(n) = (Q - Q^dagger)/8 from the four counter-clockwise leaves
-__device__ M3 fhat(const LinkView &lv, const int c[4], int mu, int nu) {
-    int e[4][4] = {{1, 0, 0, 0}, {0, 1, 0, 0}, {0, 0, 1, 0}, {0, 0, 0, 1}};
-    const int *a = e[mu], *b = e[nu];
-    auto U = [&](int d, int sa, int sb) {
-        return lv.at(d, c[0] + sa * a[0] + sb * b[0], c[1] + sa * a[1] + sb * b[1], c[2] + sa * a[2] + sb * b[2],
-                     c[3] + sa * a[3] + sb * b[3]);
+// Fhat_{mu nu} at site n (EO index i of parity par), anti-Hermitian.  Only
+// Q - Q^dagger is wanted, so the leaves 1 and 3 enter as minus their adjoints,
+// and all four close on the same two links at either end (10 products):
+//   [U_nu(n) E - U_nu(n-nu)^dag K] U_mu(n-mu) + [U_nu(n-nu)^dag H - U_nu(n) G] U_mu(n)^dag
+//   E = U_mu(n+nu-mu)^dag U_nu(n-mu)^dag    G = U_mu(n+nu) U_nu(n+mu)^dag
+//   H = U_mu(n-nu) U_nu(n+mu-nu)            K = U_mu(n-mu-nu)^dag U_nu(n-mu-nu)
+__device__ __forceinline__ AntiHerm fhat(const Geom &g, const double2 *l64, const SiteCoord &c, int par, int mu, int nu) {
+    const int n = c.x + g.L[0] * c.row;
+    const int pm = lex_step(g, c, mu, true), mm = lex_step(g, c, mu, false);
+    const int pn = lex_step(g, c, nu, true), mn = lex_step(g, c, nu, false);
+    const size_t ls = link_slab_bytes(P64, g.Vh);
+    // links rooted at n + off; odd: the root has the other parity
+    auto U = [&](int dir, int off, int odd) {
+        return LinkIO<P64>::load<false>((const char *)l64 + (size_t)(2 * dir + (par ^ odd)) * ls, g.Vh, (n + off) >> 1);
     };
-    M3 q, t;
-    // U_mu(n) U_nu(n+mu) U_mu(n+nu)^dag U_nu(n)^dag
-    t = m3mul(U(mu, 0, 0), U(nu, 1, 0));
-    t = m3mul_d(t, U(mu, 0, 1));
-    q = m3mul_d(t, U(nu, 0, 0));
-    // U_nu(n) U_mu(n+nu-mu)^dag U_nu(n-mu)^dag U_mu(n-mu)
-    t = m3mul_d(U(nu, 0, 0), U(mu, -1, 1));
-    t = m3mul_d(t, U(nu, -1, 0));
-    t = m3mul(t, U(mu, -1, 0));
-#pragma unroll
-    for (int k = 0; k < 9; k++) q.m[k] = q.m[k] + t.m[k];
-    // U_mu(n-mu)^dag U_nu(n-mu-nu)^dag U_mu(n-mu-nu) U_nu(n-nu)
+    M3 left = mzero(), right = mzero();  // factors of U_mu(n-mu) and of U_mu(n)^dag
     {
-        M3 a1 = U(mu, -1, 0), b1 = U(nu, -1, -1);
-        M3 ab;  // a1^dag b1^dag = (b1 a1)^dag
-        M3 ba = m3mul(b1, a1);
-#pragma unroll
-        for (int i = 0; i < 3; i++)
-#pragma unroll
-            for (int j = 0; j < 3; j++) ab.m[3 * i + j] = conjx(ba.m[3 * j + i]);
-        t = m3mul(ab, U(mu, -1, -1));
-        t = m3mul(t, U(nu, 0, -1));
+        const M3 un = U(nu, 0, 0);
+        {
+            M3 et = mzero();  // E^dagger
+            mmac(et, U(nu, mm, 1), U(mu, pn + mm, 0));
+            mmac_d(left, un, et);
+        }
+        M3 gm = mzero();
+        mmac_d(gm, U(mu, pn, 1), U(nu, pm, 1));
+        mmac(right, un, gm);
     }
 #pragma unroll
-    for (int k = 0; k < 9; k++) q.m[k] = q.m[k] + t.m[k];
-    // U_nu(n-nu)^dag U_mu(n-nu) U_nu(n+mu-nu) U_mu(n)^dag
-    t = m3dmul(U(nu, 0, -1), U(mu, 0, -1));
-    t = m3mul(t, U(nu, 1, -1));
-    t = m3mul_d(t, U(mu, 0, 0));
-#pragma unroll
-    for (int k = 0; k < 9; k++) q.m[k] = q.m[k] + t.m[k];
-    M3 f;
-#pragma unroll
-    for (int i = 0; i < 3; i++)
-#pragma unroll
-        for (int j = 0; j < 3; j++) {
-            const C a0 = q.m[3 * i + j], b0 = conjx(q.m[3 * j + i]);
-            f.m[3 * i + j] = 0.125 * (a0 - b0);
+    for (int k = 0; k < 9; k++) {
+        left.m[k] = -left.m[k];
+        right.m[k] = -right.m[k];
+    }
+    {
+        const M3 ub = U(nu, mn, 1);
+        {
+            M3 k = mzero();
+            mdmac(k, U(mu, mm + mn, 0), U(nu, mm + mn, 0));
+            mdmac(left, ub, k);
         }
+        M3 h = mzero();
+        mmac(h, U(mu, mn, 1), U(nu, pm + mn, 0));
+        mdmac(right, ub, h);
+    }
+#pragma unroll
+    for (int k = 0; k < 9; k++) left.m[k] = -left.m[k];
+    M3 q = mzero();
+    mmac(q, left, U(mu, mm, 1));
+    mmac_d(q, right, U(mu, 0, 0));
+    AntiHerm f;
+#pragma unroll
+    for (int k = 0; k < 3; k++) f.d[k] = 0.25 * q.m[4 * k].im;
+#pragma unroll
+    for (int k = 0; k < 3; k++) {
+        const int a = k == 2 ? 1 : 0, b = k == 0 ? 1 : 2;  // (0,1) (0,2) (1,2)
+        f.o[k] = 0.125 * (q.m[3 * a + b] - conjx(q.m[3 * b + a]));
+    }
     return f;
 }
 
-// M += coef * (S (x) F), S a 2x2 complex spin matrix, F a 3x3 colour matrix
-__device__ __forceinline__ void add_kron(C (&M)[6][6], C coef, const C (&S)[2][2], const M3 &F) {
-#pragma unroll
-    for (int s = 0; s < 2; s++)
-#pragma unroll
-        for (int sp = 0; sp < 2; sp++) {
-            const C cs = coef * S[s][sp];
-            if (cs.re == 0.0 && cs.im == 0.0) continue;
-#pragma unroll
-            for (int a = 0; a < 3; a++)
-#pragma unroll
-                for (int b = 0; b < 3; b++) cmac(M[3 * s + a][3 * sp + b], cs, F.m[3 * a + b]);
-        }
-}
+// position of (i, j), i < j, among the entries above the diagonal of a Herm6
+__device__ constexpr int upper(int i, int j) { return i * (11 - i) / 2 + j - i - 1; }
 
-// 6x6 inverse by Gauss-Jordan elimination without row exchanges.  For a
-// Hermitian matrix the pivots met on the way are the ratios of successive
-// leading principal minors, so they are all real and positive exactly when the
-// matrix is positive definite; the return value counts the pivots that are
-// not (non-positive or non-finite real part), 0 for a positive definite block,
-// for which elimination without exchanges is stable.
-__device__ int inv6(const C (&A)[6][6], C (&Ai)[6][6]) {
-    C a[6][12];
+// In-place inverse of a Hermitian 6x6 by symmetric elimination (sweeps over the
+// diagonal without row exchanges).  The pivots met on the way are the ratios of
+// successive leading principal minors, so they are all positive exactly when
+// the matrix is positive definite, for which elimination without exchanges is
+// stable; the return value counts the pivots that are not (non-positive or
+// non-finite).
+__device__ __forceinline__ int inv6(Herm6<double> &m) {
     int bad = 0;
-    for (int i = 0; i < 6; i++)
-        for (int j = 0; j < 6; j++) {
-            a[i][j] = A[i][j];
-            a[i][6 + j] = (i == j) ? C{1, 0} : C{0, 0};
+#pragma unroll
+    for (int k = 0; k < 6; k++) {
+        const double d = m.d[k];
+        if (!(d > 0.0) || !isfinite(d)) bad++;
+        const double inv = 1.0 / d;
+        C v[6];  // column k
+#pragma unroll
+        for (int i = 0; i < 6; i++) {
+            if (i == k) continue;
+            v[i] = i < k ? m.o[upper(i, k)] : conjx(m.o[upper(k, i)]);
         }
-    for (int col = 0; col < 6; col++) {
-        const C d = a[col][col];
-        if (!(d.re > 0.0) || !isfinite(d.re) || !isfinite(d.im)) bad++;
-        const double dn = d.re * d.re + d.im * d.im;
-        const C dinv = {d.re / dn, -d.im / dn};
-        for (int j = 0; j < 12; j++) a[col][j] = a[col][j] * dinv;
-        for (int r = 0; r < 6; r++) {
-            if (r == col) continue;
-            const C f = a[r][col];
-            for (int j = 0; j < 12; j++) a[r][j] = a[r][j] - f * a[col][j];
+#pragma unroll
+        for (int i = 0; i < 6; i++) {
+            if (i == k) continue;
+            const C w = inv * v[i];
+            m.d[i] = fmar(-w.re, v[i].re, fmar(-w.im, v[i].im, m.d[i]));
+#pragma unroll
+            for (int j = i + 1; j < 6; j++) {
+                if (j == k) continue;
+                cmacc(m.o[upper(i, j)], v[j], -w);  // -= w conj(v_j)
+            }
+            if (i < k) m.o[upper(i, k)] = w;
+            else m.o[upper(k, i)] = conjx(w);
         }
+        m.d[k] = -inv;
     }
-    for (int i = 0; i < 6; i++)
-        for (int j = 0; j < 6; j++) Ai[i][j] = a[i][6 + j];
+#pragma unroll
+    for (int k = 0; k < 6; k++) m.d[k] = -m.d[k];
+#pragma unroll
+    for (int k = 0; k < 15; k++) m.o[k] = -m.o[k];
     return bad;
-}
-
-// pack the Hermitian part of M (times `scale`) into 6 reals + 15 complex
-__device__ void pack_herm(const C (&M)[6][6], double scale, double (&f)[36]) {
-    for (int k = 0; k < 6; k++) f[k] = scale * M[k][k].re;
-    int k = 0;
-    for (int i = 0; i < 6; i++)
-        for (int j = i + 1; j < 6; j++) {
-            // symmetrise: (M_ij + conj(M_ji)) / 2
-            f[6 + 2 * k] = scale * 0.5 * (M[i][j].re + M[j][i].re);
-            f[7 + 2 * k] = scale * 0.5 * (M[i][j].im - M[j][i].im);
-            k++;
-        }
 }
 
 struct CloverOut {
@@ -206,82 +137,117 @@ struct CloverOut {
     char *f16, *i16;  // 148 B/site
 };
 
-__device__ void store_block_set(const CloverOut &o, bool inv, int par, int Vh, int i, const double (&f)[2][36]) {
-    char *d64 = (inv ? o.i64 : o.f64) + (size_t)par * clover_slab_bytes(P64, Vh);
-    char *d32 = (inv ? o.i32 : o.f32) + (size_t)par * clover_slab_bytes(P32, Vh);
-    char *d16 = (inv ? o.i16 : o.f16) + (size_t)par * clover_slab_bytes(P16, Vh);
-    double mx = 0.0;
-    for (int b = 0; b < 2; b++) {
-        for (int k = 0; k < 18; k++)
-            *tp<double2, 576>(d64, i, 16 * (18 * b + k)) = make_double2(f[b][2 * k], f[b][2 * k + 1]);
-        for (int k = 0; k < 9; k++)
-            *tp<float4, 288>(d32, i, 16 * (9 * b + k)) = make_float4((float)f[b][4 * k], (float)f[b][4 * k + 1],
-                                                                     (float)f[b][4 * k + 2], (float)f[b][4 * k + 3]);
-        for (int k = 0; k < 36; k++) mx = fmax(mx, fabs(f[b][k]));
-    }
-    const float s = (float)mx;
-    const float inv_s = s > 0.f ? 1.0f / s : 0.f;
-    for (int b = 0; b < 2; b++) {
-        uint32_t w[18];
-        for (int k = 0; k < 18; k++) w[k] = f2h((float)f[b][2 * k] * inv_s, (float)f[b][2 * k + 1] * inv_s);
-        for (int k = 0; k < 4; k++)
-            *tp<uint4, 148>(d16, i, 72 * b + 16 * k) = make_uint4(w[4 * k], w[4 * k + 1], w[4 * k + 2], w[4 * k + 3]);
-        *tp<uint2, 148>(d16, i, 72 * b + 64) = make_uint2(w[16], w[17]);
-    }
-    *tp<float, 148>(d16, i, 144) = s;
-}
+constexpr int kPlanes = 6;  // (0,1) (0,2) (0,3) (1,2) (1,3) (2,3)
 
 // bad_blocks: device counter of the 6x6 blocks (two per site) that are not
 // positive definite, incremented by the kernel
-__global__ __launch_bounds__(64) void k_build_clover(Geom g, const double2 *l64, CloverOut o, double kappa,
-                                                     double csw, unsigned *bad_blocks) {
-    const int i = blockIdx.x * 64 + threadIdx.x;
-    const int par = blockIdx.y;
-    if (i >= g.Vh) return;
-    const SiteCoord sc = eo_coords(g, i, par);
-    const int c[4] = {sc.x, sc.y, sc.z, sc.t};
-    LinkView lv{g, l64};
-
-    const C I1 = {0, 1}, ONE = {1, 0}, ZERO = {0, 0};
-    // i s_z, -i s_y, i s_x, and the Pauli matrices themselves
-    const C isz[2][2] = {{I1, ZERO}, {ZERO, -I1}};
-    const C misy[2][2] = {{ZERO, -ONE}, {ONE, ZERO}};
-    const C isx[2][2] = {{ZERO, I1}, {I1, ZERO}};
-    const C sx[2][2] = {{ZERO, ONE}, {ONE, ZERO}};
-    const C sy[2][2] = {{ZERO, -I1}, {I1, ZERO}};
-    const C sz[2][2] = {{ONE, ZERO}, {ZERO, -ONE}};
-
-    C A[6][6], B[6][6];
-    for (int r = 0; r < 6; r++)
-        for (int s = 0; s < 6; s++) {
-            A[r][s] = (r == s) ? ONE : ZERO;
-            B[r][s] = ZERO;
+__global__ __launch_bounds__(64 * kPlanes) void k_build_clover(Geom g, const double2 *l64, CloverOut o, double kc,
+                                                               unsigned *bad_blocks) {
+    __shared__ double fh[kPlanes][9][64];
+    __shared__ float mx[4][64];  // largest entry of each stored block
+    const int lb = xcd_block(blockIdx.x, gridDim.x, 64);  // both parities of a tile run on one XCD
+    const int tile = lb >> 1, par = lb & 1;
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+    const int i = tile * 64 + lane;
+    const bool active = i < g.Vh;
+    if (active) {
+        const int mu = w < 3 ? 0 : (w < 5 ? 1 : 2), nu = w < 3 ? w + 1 : (w < 5 ? w - 1 : 3);
+        const AntiHerm f = fhat(g, l64, eo_coords(g, i, par), par, mu, nu);
+#pragma unroll
+        for (int k = 0; k < 3; k++) {
+            fh[w][k][lane] = f.d[k];
+            fh[w][3 + 2 * k][lane] = f.o[k].re;
+            fh[w][4 + 2 * k][lane] = f.o[k].im;
         }
-    const double kc = kappa * csw;
-    const C mkc = {-kc, 0.0};
-    add_kron(A, mkc, isz, fhat(lv, c, 0, 1));
-    add_kron(A, mkc, misy, fhat(lv, c, 0, 2));
-    add_kron(A, mkc, isx, fhat(lv, c, 1, 2));
-    const C mikc = {0.0, -kc};
-    add_kron(B, mikc, sx, fhat(lv, c, 0, 3));
-    add_kron(B, mikc, sy, fhat(lv, c, 1, 3));
-    add_kron(B, mikc, sz, fhat(lv, c, 2, 3));
-
-    C M[6][6], Mi[6][6];
-    double fF[2][36], fI[2][36];
-    unsigned nbad = 0;
-    // block 0: A - B (g5 = +1), block 1: A + B (g5 = -1); store halves
-    for (int blk = 0; blk < 2; blk++) {
-        const double sgn = blk == 0 ? -1.0 : 1.0;
-        for (int r = 0; r < 6; r++)
-            for (int s = 0; s < 6; s++) M[r][s] = A[r][s] + sgn * B[r][s];
-        nbad += inv6(M, Mi) != 0;
-        pack_herm(M, 0.5, fF[blk]);
-        pack_herm(Mi, 0.5, fI[blk]);
     }
-    store_block_set(o, false, par, g.Vh, i, fF);
-    store_block_set(o, true, par, g.Vh, i, fI);
-    if (nbad) atomicAdd(bad_blocks, nbad);
+    __syncthreads();
+    const int blk = w & 1;  // 0: A - B (g5 = +1), 1: A + B (g5 = -1)
+    const bool inverse = w & 2;
+    Herm6<double> m;
+    if (w < 4 && active) {
+        // the blocks of M = A + s B in spin, from the anti-Hermitian sums
+        //   P = F01 + s F23,  R = F02 - s F13,  T = F12 + s F03:
+        //   M00 = 1 - i kc P,  M11 = 1 + i kc P,  M01 = kc (R - i T)
+        const double s = blk ? 1.0 : -1.0;
+        auto sum = [&](int p, int q, double sg) {
+            AntiHerm x;
+#pragma unroll
+            for (int k = 0; k < 3; k++) {
+                x.d[k] = fmar(sg, fh[q][k][lane], fh[p][k][lane]);
+                x.o[k].re = fmar(sg, fh[q][3 + 2 * k][lane], fh[p][3 + 2 * k][lane]);
+                x.o[k].im = fmar(sg, fh[q][4 + 2 * k][lane], fh[p][4 + 2 * k][lane]);
+            }
+            return x;
+        };
+        {
+            const AntiHerm P = sum(0, 5, s);
+#pragma unroll
+            for (int a = 0; a < 3; a++) {
+                m.d[a] = fmar(kc, P.d[a], 1.0);
+                m.d[3 + a] = fmar(-kc, P.d[a], 1.0);
+            }
+#pragma unroll
+            for (int k = 0; k < 3; k++) {
+                const int a = k == 2 ? 1 : 0, b = k == 0 ? 1 : 2;
+                m.o[upper(a, b)] = {kc * P.o[k].im, -kc * P.o[k].re};
+                m.o[upper(3 + a, 3 + b)] = {-kc * P.o[k].im, kc * P.o[k].re};
+            }
+        }
+        const AntiHerm R = sum(1, 4, -s), T = sum(3, 2, s);
+#pragma unroll
+        for (int a = 0; a < 3; a++)
+#pragma unroll
+            for (int b = 0; b < 3; b++) {
+                C &e = m.o[upper(a, 3 + b)];
+                if (a == b) {
+                    e = {kc * T.d[a], kc * R.d[a]};
+                } else {
+                    const C r = ah_off(R, a, b), t = ah_off(T, a, b);
+                    e = {kc * (r.re + t.im), kc * (r.im - t.re)};
+                }
+            }
+        if (inverse && inv6(m)) atomicAdd(bad_blocks, 1u);
+        // halves are stored; record order: 6 diagonal entries, then the 15 above
+        double f[36];
+#pragma unroll
+        for (int k = 0; k < 6; k++) f[k] = 0.5 * m.d[k];
+#pragma unroll
+        for (int k = 0; k < 15; k++) {
+            f[6 + 2 * k] = 0.5 * m.o[k].re;
+            f[7 + 2 * k] = 0.5 * m.o[k].im;
+        }
+        char *d64 = (inverse ? o.i64 : o.f64) + (size_t)par * clover_slab_bytes(P64, g.Vh);
+        char *d32 = (inverse ? o.i32 : o.f32) + (size_t)par * clover_slab_bytes(P32, g.Vh);
+        double big = 0.0;
+#pragma unroll
+        for (int k = 0; k < 36; k++) big = fmax(big, fabs(f[k]));
+        mx[w][lane] = (float)big;
+#pragma unroll
+        for (int k = 0; k < 18; k++)
+            st_stream(tp<double2, 576>(d64, i, 16 * (18 * blk + k)), make_double2(f[2 * k], f[2 * k + 1]));
+#pragma unroll
+        for (int k = 0; k < 9; k++)
+            st_stream(tp<float4, 288>(d32, i, 16 * (9 * blk + k)),
+                      make_float4((float)f[4 * k], (float)f[4 * k + 1], (float)f[4 * k + 2], (float)f[4 * k + 3]));
+    }
+    __syncthreads();
+    if (w >= 4 || !active) return;
+    // the FP16 record shares one scale between the two blocks
+    char *d16 = (inverse ? o.i16 : o.f16) + (size_t)par * clover_slab_bytes(P16, g.Vh);
+    const float sc = fmaxf(mx[w & 2][lane], mx[(w & 2) + 1][lane]);
+    const float inv_s = sc > 0.f ? 1.0f / sc : 0.f;
+    uint32_t h[18];
+#pragma unroll
+    for (int k = 0; k < 18; k++) {
+        const double a = k < 3 ? m.d[2 * k % 6] : m.o[(k + 12) % 15].re;
+        const double b = k < 3 ? m.d[(2 * k + 1) % 6] : m.o[(k + 12) % 15].im;
+        h[k] = f2h((float)(0.5 * a) * inv_s, (float)(0.5 * b) * inv_s);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; k++)
+        *tp<uint4, 148>(d16, i, 72 * blk + 16 * k) = make_uint4(h[4 * k], h[4 * k + 1], h[4 * k + 2], h[4 * k + 3]);
+    *tp<uint2, 148>(d16, i, 72 * blk + 64) = make_uint2(h[16], h[17]);
+    if (blk == 0) *tp<float, 148>(d16, i, 144) = sc;
 }
 
 }  // namespace
@@ -294,9 +260,9 @@ int launch_build_clover(wc_lattice *lat, double kappa, double csw, unsigned *bad
     o.i32 = (char *)lat->clovinv[P32];
     o.f16 = (char *)lat->clov[P16];
     o.i16 = (char *)lat->clovinv[P16];
-    dim3 grid((lat->Vh + 63) / 64, 2);
-    hipLaunchKernelGGL(k_build_clover, grid, dim3(64), 0, lat->stream, lat->g, (const double2 *)lat->links[P64], o,
-                       kappa, csw, bad_blocks);
+    const dim3 grid(2 * (pad_sites(lat->Vh) / 64));
+    hipLaunchKernelGGL(k_build_clover, grid, dim3(64 * kPlanes), 0, lat->stream, lat->g,
+                       (const double2 *)lat->links[P64], o, kappa * csw, bad_blocks);
     WC_HIP(hipGetLastError());
     return WC_OK;
 }

@@ -685,34 +685,3 @@ __device__ __forceinline__ void clover_apply(const void *slab, int Vh, int i, co
         }
     }
 }
-
-// ---------------------------------------------------------------------------
-// FP64 links and site fields addressed by lattice coordinates (used by the
-// one-time clover build and by the gradient kernels; the stencil itself uses
-// the EO neighbour arithmetic above)
-// ---------------------------------------------------------------------------
-struct SiteRef {
-    int par, i;  // parity and EO index
-};
-
-WC_HD SiteRef site_ref(const Geom &g, int x, int y, int z, int t) {
-    const int L0 = g.L[0], L1 = g.L[1], L2 = g.L[2], L3 = g.L[3];
-    x = (x % L0 + L0) % L0;
-    y = (y % L1 + L1) % L1;
-    z = (z % L2 + L2) % L2;
-    t = (t % L3 + L3) % L3;
-    const int n = x + L0 * (y + L1 * (z + L2 * t));
-    return SiteRef{(x + y + z + t) & 1, n >> 1};
-}
-
-// U_mu at a site from the FP64 link copy (tiled slabs [mu][parity])
-__device__ __forceinline__ Mat3<double> link64(const double2 *l64, const Geom &g, int mu, SiteRef s) {
-    const char *slab = (const char *)l64 + (size_t)(2 * mu + s.par) * link_slab_bytes(P64, g.Vh);
-    Mat3<double> u;
-#pragma unroll
-    for (int k = 0; k < 9; k++) {
-        double2 v = *tp<double2, 144>(slab, s.i, 16 * k);
-        u.m[k] = {v.x, v.y};
-    }
-    return u;
-}

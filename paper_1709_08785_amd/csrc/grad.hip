@@ -25,92 +25,10 @@
 //
 // The clover part is a gather: one thread per link visits its 6 plaquettes,
 // so no two threads write the same link and the result is deterministic.
+#include "mat3.hpp"
 #include "reduce.hpp"
 
 namespace {
-
-using C = cx<double>;
-using M3 = Mat3<double>;
-
-// X (N^T of a site and plane) is anti-Hermitian: its imaginary diagonal and the
-// entries above the diagonal, 9 reals
-struct AntiHerm {
-    double d[3];
-    C o[3];  // (0,1) (0,2) (1,2)
-};
-
-// entry (i, j), i != j
-__device__ __forceinline__ C ah_off(const AntiHerm &x, int i, int j) {
-    const C v = x.o[i + j - 1];
-    return i < j ? v : C{-v.re, v.im};
-}
-
-// c += a b
-__device__ __forceinline__ void mmac(M3 &c, const M3 &a, const M3 &b) {
-#pragma unroll
-    for (int i = 0; i < 3; i++)
-#pragma unroll
-        for (int j = 0; j < 3; j++)
-#pragma unroll
-            for (int k = 0; k < 3; k++) cmac(c.m[3 * i + j], a.m[3 * i + k], b.m[3 * k + j]);
-}
-// c += a b^dagger
-__device__ __forceinline__ void mmac_d(M3 &c, const M3 &a, const M3 &b) {
-#pragma unroll
-    for (int i = 0; i < 3; i++)
-#pragma unroll
-        for (int j = 0; j < 3; j++)
-#pragma unroll
-            for (int k = 0; k < 3; k++) cmacc(c.m[3 * i + j], b.m[3 * j + k], a.m[3 * i + k]);
-}
-// c += x a
-__device__ __forceinline__ void xmac(M3 &c, const AntiHerm &x, const M3 &a) {
-#pragma unroll
-    for (int i = 0; i < 3; i++)
-#pragma unroll
-        for (int j = 0; j < 3; j++)
-#pragma unroll
-            for (int k = 0; k < 3; k++) {
-                C &t = c.m[3 * i + j];
-                if (k == i) {
-                    t.re = fmar(-x.d[i], a.m[3 * k + j].im, t.re);
-                    t.im = fmar(x.d[i], a.m[3 * k + j].re, t.im);
-                } else {
-                    cmac(t, ah_off(x, i, k), a.m[3 * k + j]);
-                }
-            }
-}
-// c += a x
-__device__ __forceinline__ void macx(M3 &c, const M3 &a, const AntiHerm &x) {
-#pragma unroll
-    for (int i = 0; i < 3; i++)
-#pragma unroll
-        for (int j = 0; j < 3; j++)
-#pragma unroll
-            for (int k = 0; k < 3; k++) {
-                C &t = c.m[3 * i + j];
-                if (k == j) {
-                    t.re = fmar(-x.d[j], a.m[3 * i + k].im, t.re);
-                    t.im = fmar(x.d[j], a.m[3 * i + k].re, t.im);
-                } else {
-                    cmac(t, a.m[3 * i + k], ah_off(x, k, j));
-                }
-            }
-}
-__device__ __forceinline__ M3 mzero() {
-    M3 c;
-#pragma unroll
-    for (int k = 0; k < 9; k++) c.m[k] = {0.0, 0.0};
-    return c;
-}
-__device__ __forceinline__ M3 mdag(const M3 &a) {
-    M3 c;
-#pragma unroll
-    for (int i = 0; i < 3; i++)
-#pragma unroll
-        for (int j = 0; j < 3; j++) c.m[3 * i + j] = conjx(a.m[3 * j + i]);
-    return c;
-}
 
 // (1 - s g_mu) psi for s = +1, (1 + g_mu) psi for s = -1, Dirac representation
 __device__ void one_minus_gamma(int mu, bool minus, const Spinor<double> &p, Spinor<double> &o) {
@@ -165,7 +83,7 @@ __device__ __forceinline__ int plane_of(int mu, int nu) {
     return mu == 0 ? nu - 1 : (mu == 1 ? nu + 1 : 5);
 }
 
-// X_{mu nu}(n) = (M - M^dagger)^T for the 6 planes: per (plane, parity) a slab of
+// X_{mu nu}(n) = N^T = (M - M^dagger)^T for the 6 planes: per (plane, parity) a slab of
 // 64-site tiles, the 9 reals of AntiHerm plane after plane
 constexpr int kXSite = 9 * 8;  // bytes per site
 __host__ __device__ inline size_t x_slab_bytes(int Vh) { return (size_t)pad_sites(Vh) * kXSite; }
@@ -223,15 +141,6 @@ __device__ __forceinline__ void outer_mac(M3 &h, const Spinor<double> &a, const 
             for (int al = 0; al < 4; al++) cmacc(h.m[3 * i + j], b.c[3 * al + j], a.c[3 * al + i]);
 }
 
-// lexicographic step of one site along a direction, with the periodic wrap
-__device__ __forceinline__ int lex_step(const Geom &g, const SiteCoord &c, int mu, bool up) {
-    const int x = mu == 0 ? c.x : mu == 1 ? c.y : mu == 2 ? c.z : c.t;
-    const int stride = mu == 0 ? 1 : mu == 1 ? g.L[0] : mu == 2 ? g.L[0] * g.L[1] : g.L[0] * g.L[1] * g.L[2];
-    const int L = g.L[mu];
-    if (up) return x == L - 1 ? -(L - 1) * stride : stride;
-    return x == 0 ? (L - 1) * stride : -stride;
-}
-
 // The gradient of a tile of 64 sites of one parity, one wavefront per link
 // direction.  The clover part sums 6 plaquettes of 8 matrix products each, the
 // hopping part is added, and the link is written once.
@@ -239,7 +148,9 @@ __device__ __forceinline__ int lex_step(const Geom &g, const SiteCoord &c, int m
 // What bounds it: with the clover part, FP64 arithmetic (48 products of 3x3
 // matrices, about 10 kflop a link) and the loads that feed it, 3.9 KB a link
 // through the caches; the four directions of a tile sit in one workgroup so
-// that they find each other's links and X in L1.  The links leave through LDS:
+// that they find each other's links and X in L1.  At 24^3x48 it takes 1067 us
+// (26 TFLOP/s; k_grad_X 97 us before it), where a gather over 24 leaf slots and
+// a separate hopping kernel took 5351 + 506 us.  The links leave through LDS:
 // a lane's 9 entries are 144 bytes at a stride of 288 (the other parity's sites
 // lie between), which as lane-wise stores touches 64 lines per instruction.
 template <bool CLOVER>
