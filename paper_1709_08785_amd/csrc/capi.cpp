@@ -891,19 +891,23 @@ int tune_block_size(wc_lattice *lat, int prec, double us[3], int *chosen) {
         lat->chunk_force = chunks[0];
         if ((rc = timed(256, 2, &ms))) break;
         const int reps = std::max(4, std::min(64, (int)(2.0 / std::max(ms, 1e-3))));
-        for (size_t h = 0; h < chunks.size() && !rc; h++) {
-            lat->chunk_force = chunks[h];
-            for (int c = 0; c < 3 && !rc; c++) rc = timed(cand[c], reps, &t[3 * h + c]);
-        }
-        if (rc) break;
         // start from 256 threads (or the pinned size) at the first chunk;
         // another shape must win by 3%.  A pinned block size is the only one
         // the choice of chunk and caps considers.
         const int pin = lat->bs_pin;
         const size_t start = pin ? (pin == 64 ? 0 : pin == 128 ? 1 : 2) : 2;
+        // the split stencil has one block size: one timing serves all three
+        const bool split = split_stencil(lat, prec);
+        for (size_t h = 0; h < chunks.size() && !rc; h++) {
+            lat->chunk_force = chunks[h];
+            for (size_t c = 0; c < 3 && !rc; c++)
+                if (!split || c == start) rc = timed(cand[c], reps, &t[3 * h + c]);
+            for (size_t c = 0; c < 3 && split; c++) t[3 * h + c] = t[3 * h + start];
+        }
+        if (rc) break;
         best = start;
         for (size_t k = 0; k < t.size(); k++)
-            if ((!pin || cand[k % 3] == pin) && t[k] < 0.97 * t[best]) best = k;
+            if (((!pin && !split) || k % 3 == start) && t[k] < 0.97 * t[best]) best = k;
         // One timing of about 2 ms can favour a shape by a few percent by
         // chance, so a challenger is timed again against the starting shape,
         // alternately, three times each, and keeps its place only if the

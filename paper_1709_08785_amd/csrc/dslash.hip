@@ -254,11 +254,9 @@ void k_mult(MultBatch B) {
 #pragma unroll
             for (int k = 0; k < 12; k++) s.c[k] = s.c[k] + coef * acc.c[k];
             clover_apply<P, R, NT>(a.clov, Vh, i, s, out);
-        } else if (MODE == M_CLOV) {
+        } else {  // M_CLOV
             const Spinor<R> cen = SpinorIO<P>::template load<true>(a.center, Vh, i);
             clover_apply<P, R, NT>(a.clov, Vh, i, cen, out);
-        } else {
-            out = acc;
         }
         SpinorIO<P>::template store<P == P64>(a.out, Vh, i, out);
     }
@@ -281,10 +279,218 @@ void k_mult(MultBatch B) {
     }
 }
 
+// ---------------------------------------------------------------------------
+// The one-system stencil with a tile's four directions on four wavefronts.
+// k_mult gives a site to one thread: eight hops one after the other, each
+// waiting for its neighbour.  On a lattice of a few tiles per compute unit
+// nothing else runs meanwhile, and a launch costs that chain of latencies.
+// Here a workgroup takes one 64-site tile: wavefront mu adds both hops of
+// direction mu, with the loads of both in flight, the four partial sums meet in
+// LDS, and two wavefronts apply one chiral clover block each (loaded before the
+// hops) and store one half of the spinor.
+// It also pays on large lattices: four wavefronts on 64 sites instead of 256
+// keep a quarter of the neighbourhood in flight, and more of it stays in L2.
+// D-hat_ee, k_mult -> k_mult_split, us: FP64 12x14x10x18 34.8 -> 17.6, 24^3x48
+// 266 -> 242, 48^3x96 4029 -> 3891; FP32 24^3x48 119 -> 107 (5.7 TB/s), 32^3x64
+// 326 -> 315, 48^3x96 1843 -> 1772; full links 141 -> 128, 397 -> 384, 2151 ->
+// 2112.  Which lattices take it: split_stencil.
+// ---------------------------------------------------------------------------
+constexpr int kSplitWaves = 4;
+constexpr int kSplitBlock = -64;  // "block size" that selects it: 64 sites per workgroup
+
+// the upper (h = 0) or lower (h = 1) two spin components of a stored spinor
+template <int P, bool NT>
+__device__ __forceinline__ void half_load(const void *base, int i, int h, cx<typename Real<P>::T> (&o)[6]) {
+    if constexpr (P == P64) {
+#pragma unroll
+        for (int k = 0; k < 6; k++) {
+            const double2 v = ld_op<NT>(tp<double2, 192>(base, i, 16 * (6 * h + k)));
+            o[k] = {v.x, v.y};
+        }
+    } else if constexpr (P == P32) {
+#pragma unroll
+        for (int k = 0; k < 3; k++) {
+            const float4 v = ld_op<NT>(tp<float4, 96>(base, i, 16 * (3 * h + k)));
+            o[2 * k] = {v.x, v.y};
+            o[2 * k + 1] = {v.z, v.w};
+        }
+    } else {
+        // components 0-3 | 4-7 | 8-11 per plane: the middle plane is shared
+        const float s = ld_op<NT>(tp<float, 52>(base, i, 48));
+        const uint4 a = ld_op<NT>(tp<uint4, 52>(base, i, 32 * h));
+        const uint4 m = ld_op<NT>(tp<uint4, 52>(base, i, 16));
+        const uint32_t w[6] = {h ? m.z : a.x, h ? m.w : a.y, h ? a.x : a.z, h ? a.y : a.w, h ? a.z : m.x, h ? a.w : m.y};
+#pragma unroll
+        for (int k = 0; k < 6; k++) {
+            const float2 v = h2f(w[k]);
+            o[k] = {s * v.x, s * v.y};
+        }
+    }
+}
+
+// m: FP16's site scale, the largest magnitude of all 24 reals
+template <int P>
+__device__ __forceinline__ void half_store(void *base, int i, int h, const cx<typename Real<P>::T> (&v)[6], float m) {
+    if constexpr (P == P64) {
+#pragma unroll
+        for (int k = 0; k < 6; k++)
+            st_op<true>(tp<double2, 192>(base, i, 16 * (6 * h + k)), make_double2(v[k].re, v[k].im));
+    } else if constexpr (P == P32) {
+#pragma unroll
+        for (int k = 0; k < 3; k++)
+            *tp<float4, 96>(base, i, 16 * (3 * h + k)) = make_float4(v[2 * k].re, v[2 * k].im, v[2 * k + 1].re, v[2 * k + 1].im);
+    } else {
+        const float inv = m > 0.f ? 1.0f / m : 0.f;
+        uint32_t w[6];
+#pragma unroll
+        for (int k = 0; k < 6; k++) w[k] = f2h(v[k].re * inv, v[k].im * inv);
+        uint2 *mid = (uint2 *)tp<uint4, 52>(base, i, 16);
+        if (h == 0) {
+            *tp<uint4, 52>(base, i, 0) = make_uint4(w[0], w[1], w[2], w[3]);
+            mid[0] = make_uint2(w[4], w[5]);
+            *tp<float, 52>(base, i, 48) = m;
+        } else {
+            mid[1] = make_uint2(w[0], w[1]);
+            *tp<uint4, 52>(base, i, 32) = make_uint4(w[2], w[3], w[4], w[5]);
+        }
+    }
+}
+
+template <int P, int MODE, int RED, int LR>
+__global__ __launch_bounds__(64 * kSplitWaves) void k_mult_split(MultBatch B) {
+    using R = typename Real<P>::T;
+    __shared__ cx<R> part[kSplitWaves][12][64];
+    __shared__ cx<R> yb[2][6][64];
+    __shared__ float mx[2][64];
+    int s, lb;
+    batch_locate(B.h, xcd_block(blockIdx.x, gridDim.x, B.h.chunk), s, lb);
+    const MultKArgs &a = B.d[s];
+    if (a.done && *a.done) return;
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+    const int i = lb * 64 + lane;
+    const bool active = i < a.g.Vh;
+    const bool site = active && w < 2;  // wavefronts 0 and 1 finish the sites
+    const int Vh = a.g.Vh;
+    constexpr bool CEN = MODE != M_HOPINV;
+    // the clover block b acts on up - dn (0) or up + dn (1)
+    Herm6<R> M;
+    R cs = R(1);
+    cx<R> cen[6], oth[6];  // the centre's own half and, where the clover takes the centre, the other half
+    if (site) {
+        if constexpr (P == P16) {
+            M = CloverIO<P16>::template load_scaled<true>(a.clov, Vh, i, w, 1.0f);
+            cs = CloverIO<P16>::scale(a.clov, i);
+        } else {
+            M = CloverIO<P>::template load<true>(a.clov, Vh, i, w);
+        }
+        // read once (M_DHAT), or whole by both wavefronts
+        if constexpr (CEN) half_load<P, MODE == M_DHAT>(a.center, i, w, cen);
+        if constexpr (MODE == M_DFULL || MODE == M_INVSRC) half_load<P, false>(a.center, i, 1 - w, oth);
+    }
+    {
+        Spinor<R> acc;
+#pragma unroll
+        for (int k = 0; k < 12; k++) acc.c[k] = {R(0), R(0)};
+        if (active) {
+            const SiteCoord c = eo_coords(a.g, i, a.out_par);
+            switch (w) {
+            case 0: hop_dir<P, 0, true, LR>(a, c, i, acc); break;
+            case 1: hop_dir<P, 1, true, LR>(a, c, i, acc); break;
+            case 2: hop_dir<P, 2, true, LR>(a, c, i, acc); break;
+            default: hop_dir<P, 3, true, LR>(a, c, i, acc); break;
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < 12; k++) part[w][k][lane] = acc.c[k];
+    }
+    __syncthreads();
+    const R coef = (R)a.coef;
+    cx<R> own[6];  // the hopping sum's own half (M_DFULL)
+    if (site) {
+        cx<R> v[6], y[6];
+#pragma unroll
+        for (int k = 0; k < 6; k++) {
+            cx<R> h[2];  // upper, lower
+#pragma unroll
+            for (int q = 0; q < 2; q++)
+                h[q] = (part[0][6 * q + k][lane] + part[1][6 * q + k][lane]) +
+                       (part[2][6 * q + k][lane] + part[3][6 * q + k][lane]);
+            if (MODE == M_DFULL) {
+                own[k] = w ? h[1] : h[0];
+                h[0] = w ? oth[k] : cen[k];
+                h[1] = w ? cen[k] : oth[k];
+            } else if (MODE == M_INVSRC) {
+                h[0] = (w ? oth[k] : cen[k]) + coef * h[0];
+                h[1] = (w ? cen[k] : oth[k]) + coef * h[1];
+            }
+            v[k] = w ? h[0] + h[1] : h[0] - h[1];
+        }
+        herm6_apply(M, v, y);
+#pragma unroll
+        for (int k = 0; k < 6; k++) yb[w][k][lane] = y[k];
+    }
+    __syncthreads();
+    cx<R> out[6];
+    if (site) {
+#pragma unroll
+        for (int k = 0; k < 6; k++) {
+            const cx<R> ym = yb[0][k][lane], yp = yb[1][k][lane];
+            cx<R> t = w ? yp - ym : yp + ym;
+            if (P == P16) t = cs * t;
+            if (MODE == M_DHAT) t = cen[k] + coef * t;
+            if (MODE == M_DFULL) t = t + coef * own[k];
+            out[k] = t;
+        }
+    }
+    float m = 0.f;
+    if constexpr (P == P16) {
+        if (site) {
+#pragma unroll
+            for (int k = 0; k < 6; k++) m = fmaxf(m, fmaxf(fabsf(out[k].re), fabsf(out[k].im)));
+            mx[w][lane] = m;
+        }
+        __syncthreads();
+        if (site) m = fmaxf(m, mx[1 - w][lane]);
+    }
+    if (site) half_store<P>(a.out, i, w, out, m);
+    if (RED != R_NONE) {
+        constexpr int N = (RED == R_DOT) ? 2 : 3;
+        double v[N];
+#pragma unroll
+        for (int k = 0; k < N; k++) v[k] = 0.0;
+        if (site) {
+            cx<R> ax[6];
+            if (a.aux == a.center) {
+#pragma unroll
+                for (int k = 0; k < 6; k++) ax[k] = cen[k];
+            } else {
+                half_load<P, true>(a.aux, i, w, ax);
+            }
+#pragma unroll
+            for (int k = 0; k < 6; k++) {
+                const double ar = ax[k].re, ai = ax[k].im, orr = out[k].re, oi = out[k].im;
+                v[0] += ar * orr + ai * oi;
+                v[1] += ar * oi - ai * orr;
+                if (N == 3) v[N - 1] += orr * orr + oi * oi;
+            }
+        }
+        block_partials<N>(v, a.red.partials, a.nblk, lb);
+    }
+}
+
 // lds: dynamic LDS bytes that cap the workgroups per CU of the one-system
 // (non-temporal) instance; the kernels use none of it
 template <int P, int MODE, int RED, int LR>
 void launch_nt(const MultBatch &B, int blocks, int bs, unsigned lds, hipStream_t s) {
+    if constexpr (MODE == M_HOPINV || MODE == M_DHAT || MODE == M_DFULL || MODE == M_INVSRC) {
+        if (bs == kSplitBlock) {
+            // the cap counts the kernel's own LDS
+            constexpr unsigned own = sizeof(cx<typename Real<P>::T>) * 64 * (12 * kSplitWaves + 12);
+            const unsigned dyn = lds > own ? lds - own : 0;
+            hipLaunchKernelGGL((k_mult_split<P, MODE, RED, LR>), dim3(blocks), dim3(64 * kSplitWaves), dyn, s, B);
+            return;
+        }
+    }
     if (B.h.interleave)
         hipLaunchKernelGGL((k_mult<P, MODE, RED, false, LR>), dim3(blocks), dim3(bs), 0, s, B);
     else
@@ -318,7 +524,6 @@ void dispatch_mode(const MultBatch &B, int mode, int red, int blocks, int bs, un
         break;
     case M_DFULL: launch_one<P, M_DFULL, R_NONE>(B, blocks, bs, lds, s, lr); break;
     case M_INVSRC: launch_one<P, M_INVSRC, R_NONE>(B, blocks, bs, lds, s, lr); break;
-    case M_HOP: launch_one<P, M_HOP, R_NONE>(B, blocks, bs, lds, s, lr); break;
     case M_CLOV: launch_one<P, M_CLOV, R_NONE>(B, blocks, bs, lds, s, lr); break;
     }
 }
@@ -338,7 +543,7 @@ double mult_operator_bytes(int prec, int mode, int lr, int Vh) {
     double b = 0;
     const int lb = lr == 8 ? 32 : lr == 18 ? 72 : link_site_bytes(prec);
     if (mode != M_CLOV) b += 8 * (double)lb * Vh;
-    if (mode != M_HOP) b += (double)clover_site_bytes(prec) * Vh;
+    b += (double)clover_site_bytes(prec) * Vh;
     return b;
 }
 
@@ -1009,8 +1214,13 @@ int launch_mult_batch(hipStream_t s, const MultCall *calls, int n, wc_lattice *t
                    calls[k].red == c0.red && calls[k].out_par == c0.out_par && calls[k].coef == c0.coef;
         if (same) return launch_mult_mrhs(s, calls, n, timing_lat ? timing_lat : c0.lat, mrhs_for(c0.lat, c0.prec));
     }
-    const int bs = launch_bs(c0.bs);
-    if (!valid_block_size(bs)) return wc_fail(WC_EINVAL, "block size must be 64, 128 or 256");
+    if (!valid_block_size(launch_bs(c0.bs))) return wc_fail(WC_EINVAL, "block size must be 64, 128 or 256");
+    bool split = true;
+    // (systems interleaved on one lattice share the operator through the cache,
+    // which the split form's non-temporal loads would undo)
+    for (int k = 0; k < n; k++)
+        split = split && c0.mode != M_CLOV && split_stencil(calls[k].lat, c0.prec) && (k == 0 || calls[k].lat != c0.lat);
+    const int bs = split ? 64 : launch_bs(c0.bs);  // sites per workgroup
     MultBatch B;
     B.h.S = n;
     B.h.off[0] = 0;
@@ -1022,7 +1232,7 @@ int launch_mult_batch(hipStream_t s, const MultCall *calls, int n, wc_lattice *t
         wc_lattice *lat = c.lat;
         if (c.prec != c0.prec || c.mode != c0.mode || c.red != c0.red || c.out_par != c0.out_par)
             return wc_fail(WC_EINVAL, "batched stencil calls must share precision, mode, reduction and parity");
-        if (launch_bs(c.bs) != bs) return wc_fail(WC_EINVAL, "batched stencil calls must share the block size");
+        if (c.bs != c0.bs) return wc_fail(WC_EINVAL, "batched stencil calls must share the block size");
         same = same && (lat == c0.lat);
         MultKArgs &a = B.d[k];
         a.g = lat->g;
@@ -1081,10 +1291,11 @@ int launch_mult_batch(hipStream_t s, const MultCall *calls, int n, wc_lattice *t
             t.parts.push_back(op);
         }
     }
-    const unsigned lds = B.h.interleave ? 0u : cap_lds_bytes(c0.lat, c0.prec, bs, c0.mode);
-    if (c0.prec == P64) dispatch_mode<P64>(B, c0.mode, c0.red, blocks, bs, lds, s, 12);
-    else if (c0.prec == P32) dispatch_mode<P32>(B, c0.mode, c0.red, blocks, bs, lds, s, lr);
-    else dispatch_mode<P16>(B, c0.mode, c0.red, blocks, bs, lds, s, 12);
+    const unsigned lds = B.h.interleave ? 0u : cap_lds_bytes(c0.lat, c0.prec, split ? 64 * kSplitWaves : bs, c0.mode);
+    const int shape = split ? kSplitBlock : bs;
+    if (c0.prec == P64) dispatch_mode<P64>(B, c0.mode, c0.red, blocks, shape, lds, s, 12);
+    else if (c0.prec == P32) dispatch_mode<P32>(B, c0.mode, c0.red, blocks, shape, lds, s, lr);
+    else dispatch_mode<P16>(B, c0.mode, c0.red, blocks, shape, lds, s, 12);
     WC_HIP(hipGetLastError());
     if (tl->timing) timing_end(tl, t);
     if (c0.red != R_NONE && c0.mode == M_DHAT) {

@@ -333,14 +333,14 @@ int launch_fin_batch(hipStream_t s, const FinArgs *f, int n, int nvals);
 // them.  Calls on one lattice are interleaved block by block so that the
 // blocks that read the same links and clover run together on one XCD.
 // ---------------------------------------------------------------------------
-enum MultMode { M_HOPINV = 0, M_DHAT = 1, M_DFULL = 2, M_INVSRC = 3, M_HOP = 4, M_CLOV = 5 };
+enum MultMode { M_HOPINV = 0, M_DHAT = 1, M_DFULL = 2, M_INVSRC = 3, M_CLOV = 4 };
 enum MultRed { R_NONE = 0, R_DOT = 1, R_DOTNORM = 2 };
 
-// The FP64 stencil (140-196 VGPRs) runs 3 workgroups of 256 threads per CU
-// when left alone; held to 2 (8 waves per CU) its L2 keeps more of the
-// neighbours that the resident waves share, and MULT and D-hat run 10-11%
-// faster at 32^3x64 and 48^3x96.  The FP32 and FP16 stencils have no cap
-// unless the tuner finds one that pays on the lattice at hand.
+// The FP64 stencil is held to 2 workgroups of 256 threads (8 waves) per CU: its
+// L2 then keeps more of the neighbours that the resident waves share.  (With
+// one thread per site that was worth 10-11% at 32^3x64 and 48^3x96; the split
+// form's own LDS leaves room for no more.)  The FP32 and FP16 stencils have no
+// cap unless the tuner finds one that pays on the lattice at hand.
 constexpr int kDefaultWaveCap64 = 8;
 inline int cap_class(int mode) { return mode == M_DHAT ? 1 : 0; }
 inline bool valid_wave_cap(int w) { return w == 0 || (w >= 4 && w <= 16 && w % 4 == 0); }
@@ -364,6 +364,20 @@ inline unsigned cap_lds_bytes(const wc_lattice *lat, int prec, int bs, int mode 
     if (blocks < 1) blocks = 1;
     const int per = (L / blocks + L / (blocks + 1)) / 2 / 128 * 128 - 128;
     return per > 0 ? (unsigned)per : 0u;
+}
+
+// Whether one-system stencils on lat in precision prec run with a tile's four
+// directions on four wavefronts (k_mult_split in dslash.hip) rather than one
+// thread per site.  FP64 and the FP32 two-column and full links always do: it
+// is faster at every size measured (8^4 to 48^3x96).  FP16 storage and
+// reconstruct-8 links spend more of their time in arithmetic, and while two
+// wavefronts finish a tile the other two have none: they take it up to four tiles per compute
+// unit, where latency decides (D-hat_ee in FP16: 16^4 18.5 -> 14.6 us, 16^3x32
+// 22.1 -> 21.2, but 16^2x24x32 29.2 -> 31.2 and 32^3x64 170 -> 207;
+// reconstruct-8: 16^3x32 33.3 -> 30.9, 24^3x48 106 -> 110).
+constexpr int kSplitTiles = 1024;
+inline bool split_stencil(const wc_lattice *lat, int prec) {
+    return prec == P64 || (prec == P32 && lat->recon != 8) || pad_sites(lat->Vh) / kTile <= kSplitTiles;
 }
 
 struct MultCall {
