@@ -3,13 +3,33 @@
 // systems: one launch serves every active system of a solve.
 //
 // The BiCGStab coefficients never travel through the host: every update
-// kernel recomputes alpha = rho0 / <r~, q>, omega = <t, s> / ||t||^2 and
-// beta = (rho1 / rho0) (alpha / omega) from its system's device scalar block,
-// written by the preceding reductions.  rho alternates between two slots, so
-// the value that becomes rho1 never overwrites the rho0 still in use.  The
-// finalize stage of a reduction also raises the system's done flag; every
-// later kernel of the loop skips a system whose flag is set, so the host may
-// queue several iterations between convergence reads.
+// kernel computes alpha = rho0 / <r~, q>, omega = <t, s> / ||t||^2 and
+// beta = (rho1 / rho0) (alpha / omega) itself.  Every later kernel of the loop
+// skips a system whose done flag is set, so the host may queue several
+// iterations between convergence reads.
+//
+// The inner loop has two updates per iteration.  V_INNER_A takes the half step
+// s = r - alpha q, V_INNER_B the rest: x, r and p.  p needs rho1 = <r~, r> of the
+// r being formed, which is <r~, s> - omega <r~, t>: the first is summed with the
+// half step, the second with the second D-hat, so x, r and p take one pass over
+// s, t, p, q instead of two.  (<r~, s> is zero in exact arithmetic, but its
+// rounding errors are of the size of the first residuals and stay in r: left
+// out, rho drowns in them, and an FP32 solve at 8^3x16 and kappa 0.1355 no
+// longer converged.)
+//
+// A reduction is not finished by a kernel of its own: the update that consumes
+// it sums the partials in every block (in one order, so all blocks take the same
+// decisions), and block 0 records scalars and flags.  No kernel reads a word
+// that it also writes, except the done flag, which is only raised where every
+// block leaves without touching the vectors.  From kFoldPartials partials on,
+// re-reading them in every block would cost more than it saves, and a fold
+// kernel first sums them once.  The convergence test of ||r||^2 is taken by the
+// next V_INNER_A, or by FIN_CHECK before a host read; that of ||s||^2 by
+// V_INNER_B: up to a D-hat is done in vain once per inner solve, and the eleven
+// kernels of an iteration became six, or eight with the fold kernels.  Whole
+// solves, us per inner iteration before and after: 8^4 57 -> 43, FP64
+// 12x14x10x18 101 -> 68, 16^3x32 104 -> 92, 24^3x48 357 -> 323, 32^3x64 937 ->
+// 900 (with the split stencil of dslash.hip).
 #include "reduce.hpp"
 
 namespace {
@@ -31,8 +51,8 @@ template <class R> __device__ __forceinline__ cx<R> to(cx<double> a) { return {(
 // number of reduced values of each op (0: no reduction)
 __host__ __device__ constexpr int red_count(int op) {
     return op == V_NORM2 ? 2
-         : (op == V_SUB_NORM || op == V_INNER_INIT || op == V_INNER_A || op == V_OUTER_A || op == V_PIPE_INIT) ? 1
-         : (op == V_INNER_B || op == V_OUTER_B) ? 3
+         : (op == V_SUB_NORM || op == V_INNER_INIT || op == V_INNER_B || op == V_OUTER_A || op == V_PIPE_INIT) ? 1
+         : (op == V_INNER_A || op == V_OUTER_B) ? 3
          : op == V_PIPE_A ? 8
          : op == V_PIPE_B ? 5
          : 0;
@@ -47,6 +67,12 @@ template <class T> __device__ __forceinline__ void dot_acc(double &re, double &i
     im += xr * yi - xi * yr;
 }
 
+// outcome of an iteration that ended with ||r||^2 = rr and the next rho
+__device__ __forceinline__ int full_step_test(double rr, cx<double> rho, double tol2) {
+    if (rr < tol2) return DONE_FULL;
+    return !isfinite(rr) || (rho.re == 0.0 && rho.im == 0.0) ? DONE_BREAK : DONE_NO;
+}
+
 template <int OP, int P, int XP> __global__ __launch_bounds__(kBlock) void k_vec(VecBatch B) {
     using R = typename Real<P>::T;
     using RX = typename Real<XP>::T;
@@ -57,10 +83,6 @@ template <int OP, int P, int XP> __global__ __launch_bounds__(kBlock) void k_vec
     const VecCall &c = B.c[s];
     if (c.guard && c.fl[F_DONE]) return;
     const int Vh = c.Vh;
-    // inner-loop kernels take the iteration index from the device, so a
-    // captured chunk of iterations replays unchanged; the p update runs after
-    // the iteration count has been advanced
-    const int iter = c.iter_dev ? c.fl[F_ITERS] - (OP == V_INNER_C ? 1 : 0) : c.iter;
     const int i = lb * (int)blockDim.x + threadIdx.x;  // 64, 128 or 256 sites per block
     const bool active = i < Vh;
     double a[NA];
@@ -137,27 +159,78 @@ template <int OP, int P, int XP> __global__ __launch_bounds__(kBlock) void k_vec
             for (int k = 0; k < 12; k++) a[0] += norm2(bs.c[k]);
         }
     } else if (OP == V_INNER_A) {
-        // alpha = rho0 / <r~, q>;  s = r - alpha q (in place in r);  ||s||^2
-        const cx<R> alpha = to<R>(cdiv(ld_c(c.sc, rho_slot(iter)), ld_c(c.sc, S_RQ)));
+        // the last iteration's full-step test, then alpha = rho0 / <r~, q>;
+        // s = r - alpha q (in place in r);  ||s||^2, <r~, s>
+        Spinor<R> rv, qv, rtv;  // on their way while the sums are formed
         if (active) {
-            Spinor<R> rv = SpinorIO<P>::template load<kVNT>(c.a, Vh, i);
-            const Spinor<R> qv = SpinorIO<P>::template load<kVNT>(c.b, Vh, i);
+            rv = SpinorIO<P>::template load<kVNT>(c.a, Vh, i);
+            qv = SpinorIO<P>::template load<kVNT>(c.b, Vh, i);
+            rtv = SpinorIO<P>::template load<kVNT>(c.c, Vh, i);
+        }
+        double q[3];
+        sum_partials<2, 1>(c.in0, c.in1, q);
+        const cx<double> rho = ld_c(c.sc, S_RHO0), rq = {q[0], q[1]}, al = cdiv(rho, rq);
+        const int stop = c.fl[F_ITERS] > 0 ? full_step_test(q[2], rho, c.sc[S_TOL2]) : DONE_NO;
+        const bool first = lb == 0 && threadIdx.x == 0;
+        if (stop != DONE_NO || !finite_c(al)) {
+            if (first) {
+                c.fl[F_STOPPH] = stop != DONE_NO ? 2 : 1;
+                c.fl[F_DONE] = stop != DONE_NO ? stop : DONE_BREAK;
+            }
+            return;
+        }
+        if (first) {
+            c.sc[S_RQ] = rq.re;
+            c.sc[S_RQ + 1] = rq.im;
+            c.sc[S_RHO1] = rho.re;
+            c.sc[S_RHO1 + 1] = rho.im;
+        }
+        const cx<R> alpha = to<R>(al);
+        if (active) {
 #pragma unroll
             for (int k = 0; k < 12; k++) rv.c[k] = rv.c[k] - alpha * qv.c[k];
             SpinorIO<P>::template store<kVNT>(c.a, Vh, i, rv);
 #pragma unroll
-            for (int k = 0; k < 12; k++) a[0] += norm2(rv.c[k]);
+            for (int k = 0; k < 12; k++) {
+                a[0] += norm2(rv.c[k]);
+                dot_acc(a[1 % NA], a[2 % NA], rtv.c[k], rv.c[k]);
+            }
         }
     } else if (OP == V_INNER_B) {
-        // omega = <t, s> / ||t||^2;  x += alpha p + omega s;  r = s - omega t;  ||r||^2, <r~, r>
-        const cx<double> al = cdiv(ld_c(c.sc, rho_slot(iter)), ld_c(c.sc, S_RQ));
-        const double tt = c.sc[S_TT];
-        const cx<double> om = {c.sc[S_ST] / tt, -c.sc[S_ST + 1] / tt};
-        const cx<RX> alx = to<RX>(al), omx = to<RX>(om);
-        const cx<R> omega = to<R>(om);
+        // the half-step test, then omega = <t, s> / ||t||^2,
+        // rho1 = <r~, s> - omega <r~, t>, beta = (rho1 / rho0) (alpha / omega);
+        // x += alpha p + omega s;  r = s - omega t;  p = r + beta (p - omega q);  ||r||^2
+        Spinor<R> sv, pv;
         if (active) {
-            Spinor<R> sv = SpinorIO<P>::template load<kVNT>(c.b, Vh, i);
-            const Spinor<R> pv = SpinorIO<P>::template load<kVNT>(c.c, Vh, i);
+            sv = SpinorIO<P>::template load<kVNT>(c.b, Vh, i);
+            pv = SpinorIO<P>::template load<kVNT>(c.c, Vh, i);
+        }
+        double q[8];
+        sum_partials<5, 3>(c.in0, c.in1, q);
+        const double tt = q[2], ss = q[5];
+        const cx<double> rho = ld_c(c.sc, S_RHO1), al = cdiv(rho, ld_c(c.sc, S_RQ));
+        const cx<double> om = {q[0] / tt, -q[1] / tt};
+        const cx<R> omega = to<R>(om);  // as it is applied
+        const cx<double> rho1 =
+            cx<double>{q[6], q[7]} - cx<double>{(double)omega.re, (double)omega.im} * cx<double>{q[3], q[4]};
+        const bool half = !isfinite(ss) || ss < c.sc[S_TOL2];
+        const bool first = lb == 0 && threadIdx.x == 0;
+        if (half || !(tt > 0.0) || !finite_c(om)) {
+            if (first) {
+                if (!half) c.fl[F_ITERS] += 1;
+                c.fl[F_STOPPH] = half ? 1 : 2;
+                c.fl[F_DONE] = half && isfinite(ss) ? DONE_HALF : DONE_BREAK;
+            }
+            return;
+        }
+        if (first) {
+            c.sc[S_RHO0] = rho1.re;
+            c.sc[S_RHO0 + 1] = rho1.im;
+            c.fl[F_ITERS] += 1;
+        }
+        const cx<RX> alx = to<RX>(al), omx = to<RX>(om);
+        const cx<R> beta = to<R>(cdiv(rho1, rho) * cdiv(al, om));
+        if (active) {
             Spinor<RX> xv = SpinorIO<XP>::template load<kVNT>(c.a, Vh, i);
 #pragma unroll
             for (int k = 0; k < 12; k++) {
@@ -167,36 +240,35 @@ template <int OP, int P, int XP> __global__ __launch_bounds__(kBlock) void k_vec
             SpinorIO<XP>::template store<kVNT>(c.a, Vh, i, xv);
             const Spinor<R> tv = SpinorIO<P>::template load<kVNT>(c.d, Vh, i);
 #pragma unroll
-            for (int k = 0; k < 12; k++) sv.c[k] = sv.c[k] - omega * tv.c[k];
-            SpinorIO<P>::template store<kVNT>(c.b, Vh, i, sv);
-            const Spinor<R> rtv = SpinorIO<P>::template load<kVNT>(c.e, Vh, i);
-#pragma unroll
             for (int k = 0; k < 12; k++) {
+                sv.c[k] = sv.c[k] - omega * tv.c[k];
                 a[0] += norm2(sv.c[k]);
-                const double ar = rtv.c[k].re, ai = rtv.c[k].im, br = sv.c[k].re, bi = sv.c[k].im;
-                a[1 % NA] += ar * br + ai * bi;
-                a[2 % NA] += ar * bi - ai * br;
             }
+            SpinorIO<P>::template store<kVNT>(c.b, Vh, i, sv);
+            const Spinor<R> qv = SpinorIO<P>::template load<kVNT>(c.e, Vh, i);
+#pragma unroll
+            for (int k = 0; k < 12; k++) pv.c[k] = sv.c[k] + beta * (pv.c[k] - omega * qv.c[k]);
+            SpinorIO<P>::template store<kVNT>(c.c, Vh, i, pv);
         }
-    } else if (OP == V_INNER_C) {
+    } else if (OP == V_OUTER_C) {
         // beta = (rho1 / rho0) (alpha / omega);  p = r + beta (p - omega q)
         if (active) {
-            const cx<double> rho0 = ld_c(c.sc, rho_slot(iter)), rho1 = ld_c(c.sc, rho_slot(iter + 1));
+            const cx<double> rho0 = ld_c(c.sc, rho_slot(c.iter)), rho1 = ld_c(c.sc, rho_slot(c.iter + 1));
             const cx<double> al = cdiv(rho0, ld_c(c.sc, S_RQ));
             const double tt = c.sc[S_TT];
             const cx<double> om = {c.sc[S_ST] / tt, -c.sc[S_ST + 1] / tt};
-            const cx<R> beta = to<R>(cdiv(rho1, rho0) * cdiv(al, om)), omega = to<R>(om);
-            Spinor<R> pv = SpinorIO<P>::template load<kVNT>(c.a, Vh, i);
-            const Spinor<R> rv = SpinorIO<P>::template load<kVNT>(c.b, Vh, i);
-            const Spinor<R> qv = SpinorIO<P>::template load<kVNT>(c.c, Vh, i);
+            const cx<double> beta = cdiv(rho1, rho0) * cdiv(al, om);
+            Spinor<double> pv = SpinorIO<P64>::template load<kVNT>(c.a, Vh, i);
+            const Spinor<double> rv = SpinorIO<P64>::template load<kVNT>(c.b, Vh, i);
+            const Spinor<double> qv = SpinorIO<P64>::template load<kVNT>(c.c, Vh, i);
 #pragma unroll
-            for (int k = 0; k < 12; k++) pv.c[k] = rv.c[k] + beta * (pv.c[k] - omega * qv.c[k]);
-            SpinorIO<P>::template store<kVNT>(c.a, Vh, i, pv);
+            for (int k = 0; k < 12; k++) pv.c[k] = rv.c[k] + beta * (pv.c[k] - om * qv.c[k]);
+            SpinorIO<P64>::template store<kVNT>(c.a, Vh, i, pv);
         }
     } else if (OP == V_INNER_FIX) {
         // x += alpha p (the update skipped when the half step already converged)
         if (active) {
-            const cx<RX> alx = to<RX>(cdiv(ld_c(c.sc, rho_slot(iter)), ld_c(c.sc, S_RQ)));
+            const cx<RX> alx = to<RX>(cdiv(ld_c(c.sc, S_RHO1), ld_c(c.sc, S_RQ)));
             Spinor<RX> xv = SpinorIO<XP>::template load<kVNT>(c.a, Vh, i);
             const Spinor<R> pv = SpinorIO<P>::template load<kVNT>(c.b, Vh, i);
 #pragma unroll
@@ -215,7 +287,7 @@ template <int OP, int P, int XP> __global__ __launch_bounds__(kBlock) void k_vec
         }
     } else if (OP == V_OUTER_A) {
         // alpha = rho0 / <r~, q>;  x += alpha v;  r -= alpha q;  ||r||^2
-        const cx<double> al = cdiv(ld_c(c.sc, rho_slot(iter)), ld_c(c.sc, S_RQ));
+        const cx<double> al = cdiv(ld_c(c.sc, rho_slot(c.iter)), ld_c(c.sc, S_RQ));
         if (active) {
             Spinor<double> xv = SpinorIO<P64>::template load<kVNT>(c.a, Vh, i);
             Spinor<double> rv = SpinorIO<P64>::template load<kVNT>(c.b, Vh, i);
@@ -418,30 +490,12 @@ template <int N> __global__ __launch_bounds__(kBlock) void k_finalize(FinBatch B
         fl[F_ITERS] = 0;
         fl[F_STOPPH] = 0;
         break;
-    case FIN_INNER_A: {
-        const int it = fl[F_ITERS];
-        const cx<double> al = cdiv(ld_c(sc, rho_slot(it)), ld_c(sc, S_RQ));
-        sc[S_SS] = a[0];
-        if (!finite_c(al) || !isfinite(a[0])) fl[F_DONE] = DONE_BREAK;
-        else if (a[0] < sc[S_TOL2]) fl[F_DONE] = DONE_HALF;
-        if (fl[F_DONE] != DONE_NO) fl[F_STOPPH] = 1;
-        break;
-    }
-    case FIN_INNER_B: {
-        const int it = fl[F_ITERS];
-        const int nxt = rho_slot(it + 1);
-        const double tt = sc[S_TT];
-        const double tol2 = sc[S_TOL2];
-        const cx<double> om = {sc[S_ST] / tt, -sc[S_ST + 1] / tt};
-        sc[S_RR] = a[0];
-        sc[nxt] = a1;
-        sc[nxt + 1] = a2;
-        fl[F_ITERS] = it + 1;
-        if (!(tt > 0.0) || !finite_c(om) || !isfinite(a[0]) || (a1 == 0.0 && a2 == 0.0))
-            fl[F_DONE] = (a[0] < tol2) ? DONE_FULL : DONE_BREAK;
-        else if (a[0] < tol2)
-            fl[F_DONE] = DONE_FULL;
-        if (fl[F_DONE] != DONE_NO) fl[F_STOPPH] = 2;
+    case FIN_CHECK: {
+        const int stop = full_step_test(a[0], ld_c(sc, S_RHO0), sc[S_TOL2]);
+        if (stop != DONE_NO) {
+            fl[F_STOPPH] = 2;
+            fl[F_DONE] = stop;
+        }
         break;
     }
     case FIN_PIPE_INIT: {
@@ -509,6 +563,32 @@ template <int N> __global__ __launch_bounds__(kBlock) void k_finalize(FinBatch B
     }
 }
 
+// the sums of each system's two sets of partials, one block per value: large
+// enough that a lattice's partials are a few loads per thread (20736 at 48^3x96)
+constexpr int kFoldBlock = 1024;
+struct FoldBatch {
+    FoldArgs f[kMaxSys];
+    int na;
+};
+__global__ __launch_bounds__(kFoldBlock) void k_fold(FoldBatch B) {
+    const FoldArgs &f = B.f[blockIdx.y];
+    if (f.guard && *f.guard) return;
+    __shared__ double sh[kFoldBlock / 64];
+    const int k = blockIdx.x;
+    const SumSource s = k < B.na ? f.a : f.b;
+    const double *p = s.p + (size_t)(k < B.na ? k : k - B.na) * s.n;
+    double v[1] = {0.0};
+#pragma unroll 8
+    for (int j = threadIdx.x; j < s.n; j += kFoldBlock) v[0] += p[j];
+    wave_fold<1>(v);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v[0];
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    double t = 0.0;
+    for (int w = 0; w < kFoldBlock / 64; w++) t += sh[w];
+    f.out[k] = t;
+}
+
 // algorithmic bytes of one op on one system (vectors read and written)
 double vec_bytes(int op, int prec, int xprec, int Vh) {
     const double S = (double)spinor_site_bytes(prec) * Vh, X = (double)spinor_site_bytes(xprec) * Vh,
@@ -521,9 +601,8 @@ double vec_bytes(int op, int prec, int xprec, int Vh) {
     case V_ZERO: return D;
     case V_GAMMA5: return 4 * D;
     case V_INNER_INIT: return D + 3 * S + X;
-    case V_INNER_A: return 3 * S;
-    case V_INNER_B: return 5 * S + 2 * X;
-    case V_INNER_C: return 4 * S;
+    case V_INNER_A: return 4 * S;
+    case V_INNER_B: return 6 * S + 2 * X;
     case V_INNER_FIX: return S + 2 * X;
     case V_INNER_FINAL: return X + D;
     case V_OUTER_A: return 6 * D;
@@ -532,6 +611,7 @@ double vec_bytes(int op, int prec, int xprec, int Vh) {
     case V_PIPE_B: return 10 * S + 2 * X;
     case V_PIPE_FIX: return S + 2 * X;
     case V_OUTER_B: return 7 * D;
+    case V_OUTER_C: return 4 * D;
     }
     return 0;
 }
@@ -562,6 +642,15 @@ int launch_fin_batch(hipStream_t s, const FinArgs *f, int n, int nvals) {
     case 8: hipLaunchKernelGGL(k_finalize<8>, dim3(n), dim3(kBlock), 0, s, B); break;
     default: return wc_fail(WC_EINVAL, "unsupported reduction width");
     }
+    WC_HIP(hipGetLastError());
+    return WC_OK;
+}
+
+int launch_fold_batch(hipStream_t s, const FoldArgs *f, int n, int na, int nb) {
+    FoldBatch B;
+    for (int k = 0; k < n; k++) B.f[k] = f[k];
+    B.na = na;
+    hipLaunchKernelGGL(k_fold, dim3(na + nb, n), dim3(kFoldBlock), 0, s, B);
     WC_HIP(hipGetLastError());
     return WC_OK;
 }
@@ -604,7 +693,6 @@ int launch_vec_batch(hipStream_t s, wc_lattice *tlat, int op, int prec, const Ve
     case V_INNER_INIT: dispatch_inner<V_INNER_INIT>(s, B, blocks, bs, prec); break;
     case V_INNER_A: dispatch_inner<V_INNER_A>(s, B, blocks, bs, prec); break;
     case V_INNER_B: dispatch_inner<V_INNER_B>(s, B, blocks, bs, prec); break;
-    case V_INNER_C: dispatch_inner<V_INNER_C>(s, B, blocks, bs, prec); break;
     case V_INNER_FIX: dispatch_inner<V_INNER_FIX>(s, B, blocks, bs, prec); break;
     case V_INNER_FINAL: dispatch_inner<V_INNER_FINAL>(s, B, blocks, bs, prec); break;
     case V_PIPE_INIT: dispatch_inner<V_PIPE_INIT>(s, B, blocks, bs, prec); break;
@@ -613,6 +701,7 @@ int launch_vec_batch(hipStream_t s, wc_lattice *tlat, int op, int prec, const Ve
     case V_PIPE_FIX: dispatch_inner<V_PIPE_FIX>(s, B, blocks, bs, prec); break;
     case V_OUTER_A: launch_op<V_OUTER_A, P64, P64>(s, B, blocks, bs); break;
     case V_OUTER_B: launch_op<V_OUTER_B, P64, P64>(s, B, blocks, bs); break;
+    case V_OUTER_C: launch_op<V_OUTER_C, P64, P64>(s, B, blocks, bs); break;
     default: return wc_fail(WC_EINVAL, "unknown vector op");
     }
     WC_HIP(hipGetLastError());
@@ -620,7 +709,7 @@ int launch_vec_batch(hipStream_t s, wc_lattice *tlat, int op, int prec, const Ve
 
     // second stage of the reductions
     const int N = red_count(op);
-    if (N == 0) return WC_OK;
+    if (N == 0 || op == V_INNER_A || op == V_INNER_B) return WC_OK;  // the next update sums these
     FinArgs f[kMaxSys];
     for (int k = 0; k < n; k++) {
         const VecCall &c = calls[k];
@@ -635,8 +724,6 @@ int launch_vec_batch(hipStream_t s, wc_lattice *tlat, int op, int prec, const Ve
         a.iter = c.iter;
         a.tol2 = c.tol2;
         a.op = (op == V_INNER_INIT || op == V_PIPE_INIT) ? FIN_INIT
-             : (op == V_INNER_A)                          ? FIN_INNER_A
-             : (op == V_INNER_B)                          ? FIN_INNER_B
              : (op == V_OUTER_B)                          ? FIN_OUTER_B
              : (op == V_PIPE_A)                           ? FIN_PIPE_A
              : (op == V_PIPE_B)                           ? FIN_PIPE_B

@@ -302,7 +302,7 @@ extern "C" int wc_create_lattice(const int dims[4], void *stream, wc_lattice **o
     if (!rc) {
         arena_bind(lat->arena, 0, lat->sys);
         rc = dev_alloc((void **)&lat->sys.partials,
-                       sizeof(double) * kMaxRed * (size_t)blocks_of(lat->Vh, kMinBlock));
+                       sizeof(double) * PS_COUNT * (size_t)blocks_of(lat->Vh, kMinBlock));
         if (!rc) rc = dev_alloc((void **)&lat->sys.partials2, sizeof(double) * kMaxRed * (size_t)lat->nblocks);
         const size_t bar_bytes = sizeof(unsigned long long) * ((size_t)lat->nblocks + 2);
         if (!rc) rc = dev_alloc((void **)&lat->sys.bar, bar_bytes);
@@ -474,7 +474,7 @@ extern "C" int wc_solve_multi(int n, wc_lattice *const *lats, const void *const 
         for (int k = 0; k < n; k++) {
             arena_bind(bc->arena, k, bc->sys[k]);
             if (int rc = buf_get((void **)&bc->sys[k].partials, &bc->sys[k].partials_bytes,
-                                 sizeof(double) * kMaxRed * (size_t)blocks_of(lats[k]->Vh, kMinBlock),
+                                 sizeof(double) * PS_COUNT * (size_t)blocks_of(lats[k]->Vh, kMinBlock),
                                  lead->stream)) {
                 restore();
                 return rc;
@@ -895,9 +895,12 @@ int tune_block_size(wc_lattice *lat, int prec, double us[3], int *chosen) {
         // another shape must win by 3%.  A pinned block size is the only one
         // the choice of chunk and caps considers.
         const int pin = lat->bs_pin;
-        const size_t start = pin ? (pin == 64 ? 0 : pin == 128 ? 1 : 2) : 2;
-        // the split stencil has one block size: one timing serves all three
+        // The split stencil has one block size, so one timing serves all three
+        // and the size is that of the vector kernels alone: 64 while that still
+        // gives every compute unit at most one block, 256 above.
         const bool split = split_stencil(lat, prec);
+        const int bs0 = pin ? pin : (split && pad_sites(lat->Vh) / kTile <= 256) ? 64 : 256;
+        const size_t start = bs0 == 64 ? 0 : bs0 == 128 ? 1 : 2;
         for (size_t h = 0; h < chunks.size() && !rc; h++) {
             lat->chunk_force = chunks[h];
             for (size_t c = 0; c < 3 && !rc; c++)

@@ -249,6 +249,9 @@ template <bool NT, class T> __device__ __forceinline__ T ld_op(const T *p) {
 __device__ __forceinline__ void keep(float2 &v) {
     asm volatile("" : "+v"(v.x), "+v"(v.y));
 }
+template <class R> __device__ __forceinline__ void keep(cx<R> &v) {
+    asm volatile("" : "+v"(v.re), "+v"(v.im));
+}
 __device__ __forceinline__ float2 h2f(uint32_t u) {
     __half2 h = *reinterpret_cast<__half2 *>(&u);
     return __half22float2(h);

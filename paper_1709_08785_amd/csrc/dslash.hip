@@ -46,6 +46,21 @@ struct MultBatch {
     MultKArgs d[kMaxSys];
 };
 
+// the fused reductions: v[0..1] += <ax, out>, and with NORM v[2] += ||out||^2
+template <bool DOT, bool NORM, int NC, class R>
+__device__ __forceinline__ void red_add(double *v, const cx<R> *ax, const cx<R> *out) {
+#pragma unroll
+    for (int k = 0; k < NC; k++) {
+        const double orr = out[k].re, oi = out[k].im;
+        if (DOT) {
+            const double ar = ax[k].re, ai = ax[k].im;
+            v[0] += ar * orr + ai * oi;
+            v[1] += ar * oi - ai * orr;
+        }
+        if (NORM) v[2] += orr * orr + oi * oi;
+    }
+}
+
 // g = U h (dag = false) or U^dagger h (dag = true), two spin components
 template <class R, bool DAG>
 __device__ __forceinline__ void su3_mul2(const Mat3<R> &U, const cx<R> (&h)[2][3], cx<R> (&g)[2][3]) {
@@ -220,8 +235,8 @@ void k_mult(MultBatch B) {
     const bool active = i < a.g.Vh;
     const int Vh = a.g.Vh;
     Spinor<R> out;
-    // the fused reduction's operand: the centre vector itself when aux is the
-    // centre (read once), else loaded after the output is stored
+    // R_STEP's first operand, the centre vector (read once); the other operand
+    // is loaded after the output is stored
     Spinor<R> ax;
     if (active) {
         Spinor<R> acc;
@@ -241,7 +256,7 @@ void k_mult(MultBatch B) {
             Spinor<R> t;
             clover_apply<P, R, NT>(a.clov, Vh, i, acc, t);
             const Spinor<R> cen = SpinorIO<P>::template load<true>(a.center, Vh, i);
-            if (RED != R_NONE && a.aux == a.center) ax = cen;
+            if (RED == R_STEP) ax = cen;
 #pragma unroll
             for (int k = 0; k < 12; k++) out.c[k] = cen.c[k] + coef * t.c[k];
         } else if (MODE == M_DFULL) {
@@ -260,19 +275,17 @@ void k_mult(MultBatch B) {
         }
         SpinorIO<P>::template store<P == P64>(a.out, Vh, i, out);
     }
-    if (RED != R_NONE) {
-        constexpr int N = (RED == R_DOT) ? 2 : 3;
+    if constexpr (RED != R_NONE) {
+        constexpr int N = red_values(RED);
         double v[N];
 #pragma unroll
         for (int k = 0; k < N; k++) v[k] = 0.0;
         if (active) {
-            if (!(MODE == M_DHAT && a.aux == a.center)) ax = SpinorIO<P>::template load<true>(a.aux, Vh, i);
-#pragma unroll
-            for (int k = 0; k < 12; k++) {
-                const double ar = ax.c[k].re, ai = ax.c[k].im, orr = out.c[k].re, oi = out.c[k].im;
-                v[0] += ar * orr + ai * oi;
-                v[1] += ar * oi - ai * orr;
-                if (N == 3) v[N - 1] += orr * orr + oi * oi;
+            if (RED == R_STEP) {
+                red_add<true, true, 12>(v, ax.c, out.c);
+                red_add<true, false, 12>(v + 3, SpinorIO<P>::template load<true>(a.aux, Vh, i).c, out.c);
+            } else {
+                red_add<true, RED == R_DOTNORM, 12>(v, SpinorIO<P>::template load<true>(a.aux, Vh, i).c, out.c);
             }
         }
         block_partials<N>(v, a.red.partials, a.nblk, lb);
@@ -356,8 +369,14 @@ __device__ __forceinline__ void half_store(void *base, int i, int h, const cx<ty
     }
 }
 
+// Held to the waves per SIMD that the loads of a direction leave registers for
+// (the reductions alone would cost the FP32 D-hat half its fourth wave).
+template <int P, int MODE, int LR> constexpr int split_waves() {
+    return P == P64 ? 2 : (LR == 8 || MODE == M_DFULL || MODE == M_INVSRC) ? 3 : 4;
+}
 template <int P, int MODE, int RED, int LR>
-__global__ __launch_bounds__(64 * kSplitWaves) void k_mult_split(MultBatch B) {
+__global__ __launch_bounds__(64 * kSplitWaves) __attribute__((amdgpu_waves_per_eu(split_waves<P, MODE, LR>())))
+void k_mult_split(MultBatch B) {
     using R = typename Real<P>::T;
     __shared__ cx<R> part[kSplitWaves][12][64];
     __shared__ cx<R> yb[2][6][64];
@@ -383,9 +402,13 @@ __global__ __launch_bounds__(64 * kSplitWaves) void k_mult_split(MultBatch B) {
         } else {
             M = CloverIO<P>::template load<true>(a.clov, Vh, i, w);
         }
-        // read once (M_DHAT), or whole by both wavefronts
-        if constexpr (CEN) half_load<P, MODE == M_DHAT>(a.center, i, w, cen);
+        // (both wavefronts read the whole centre here, through the cache)
         if constexpr (MODE == M_DFULL || MODE == M_INVSRC) half_load<P, false>(a.center, i, 1 - w, oth);
+    }
+    // wavefronts 2 and 3 hold a half of the fused dot's operand in its place
+    if constexpr (CEN) {
+        if (RED != R_NONE ? active : site)
+            half_load<P, MODE == M_DHAT>(RED != R_NONE && w >= 2 ? a.aux : a.center, i, w & 1, cen);
     }
     {
         Spinor<R> acc;
@@ -453,26 +476,28 @@ __global__ __launch_bounds__(64 * kSplitWaves) void k_mult_split(MultBatch B) {
         if (site) m = fmaxf(m, mx[1 - w][lane]);
     }
     if (site) half_store<P>(a.out, i, w, out, m);
-    if (RED != R_NONE) {
-        constexpr int N = (RED == R_DOT) ? 2 : 3;
+    if constexpr (RED != R_NONE) {
+        // wavefronts 0 and 1 sum what they hold, 2 and 3 the dot with the
+        // operand they loaded
+        constexpr int N = red_values(RED);
         double v[N];
 #pragma unroll
         for (int k = 0; k < N; k++) v[k] = 0.0;
+        // (left to itself the compiler widens the operand to FP64 where it is
+        // loaded, and the hops lose the registers)
+#pragma unroll
+        for (int k = 0; k < 6; k++) keep(cen[k]);
         if (site) {
-            cx<R> ax[6];
-            if (a.aux == a.center) {
 #pragma unroll
-                for (int k = 0; k < 6; k++) ax[k] = cen[k];
-            } else {
-                half_load<P, true>(a.aux, i, w, ax);
-            }
+            for (int k = 0; k < 6; k++) part[w][k][lane] = out[k];
+            red_add<RED == R_STEP, RED != R_DOT, 6>(v, cen, out);
+        }
+        __syncthreads();
+        if (active && w >= 2) {
+            cx<R> o[6];
 #pragma unroll
-            for (int k = 0; k < 6; k++) {
-                const double ar = ax[k].re, ai = ax[k].im, orr = out[k].re, oi = out[k].im;
-                v[0] += ar * orr + ai * oi;
-                v[1] += ar * oi - ai * orr;
-                if (N == 3) v[N - 1] += orr * orr + oi * oi;
-            }
+            for (int k = 0; k < 6; k++) o[k] = part[w - 2][k][lane];
+            red_add<true, false, 6>(RED == R_STEP ? v + 3 : v, cen, o);
         }
         block_partials<N>(v, a.red.partials, a.nblk, lb);
     }
@@ -519,8 +544,10 @@ void dispatch_mode(const MultBatch &B, int mode, int red, int blocks, int bs, un
     case M_HOPINV: launch_one<P, M_HOPINV, R_NONE>(B, blocks, bs, lds, s, lr); break;
     case M_DHAT:
         if (red == R_DOT) launch_one<P, M_DHAT, R_DOT>(B, blocks, bs, lds, s, lr);
-        else if (red == R_DOTNORM) launch_one<P, M_DHAT, R_DOTNORM>(B, blocks, bs, lds, s, lr);
-        else launch_one<P, M_DHAT, R_NONE>(B, blocks, bs, lds, s, lr);
+        else if (red == R_STEP) launch_one<P, M_DHAT, R_STEP>(B, blocks, bs, lds, s, lr);
+        else if (red == R_DOTNORM) {
+            if constexpr (P == P64) launch_one<P, M_DHAT, R_DOTNORM>(B, blocks, bs, lds, s, lr);  // outer loop only
+        } else launch_one<P, M_DHAT, R_NONE>(B, blocks, bs, lds, s, lr);
         break;
     case M_DFULL: launch_one<P, M_DFULL, R_NONE>(B, blocks, bs, lds, s, lr); break;
     case M_INVSRC: launch_one<P, M_INVSRC, R_NONE>(B, blocks, bs, lds, s, lr); break;
@@ -532,11 +559,11 @@ void dispatch_mode(const MultBatch &B, int mode, int red, int blocks, int bs, un
 // stored precision, each link once, one clover pair).  The spinor part is per
 // call; the link and clover part is per lattice, since calls of one batch on
 // the same lattice read the same operator.
-double mult_spinor_bytes(int prec, int mode, int red, bool aux_is_centre, int Vh) {
+double mult_spinor_bytes(int prec, int mode, int red, int Vh) {
     const double S = (double)spinor_site_bytes(prec) * Vh;
     double b = 2 * S;                                                    // input (once) + output
     if (mode == M_DHAT || mode == M_DFULL || mode == M_INVSRC) b += S;  // centre vector
-    if (red != R_NONE && !aux_is_centre) b += S;                         // aux vector, unless the centre
+    if (red != R_NONE) b += S;                                           // aux vector
     return b;
 }
 double mult_operator_bytes(int prec, int mode, int lr, int Vh) {
@@ -676,7 +703,7 @@ __global__ __launch_bounds__(64 * kMrhsMaxGroups) void k_mult_mrhs(MrhsArgs A) {
     const int Vh = A.g.Vh;
     const int i = tile * 64 + (int)(threadIdx.x & 63);
     const bool active = i < Vh;
-    constexpr int NR = (RED == R_DOTNORM) ? 3 : 2;  // values of the fused reduction
+    constexpr int NR = RED == R_NONE ? 1 : red_values(RED);  // values of the fused reduction
     double red[G][NR];
 #pragma unroll
     for (int j = 0; j < G; j++)
@@ -700,22 +727,17 @@ __global__ __launch_bounds__(64 * kMrhsMaxGroups) void k_mult_mrhs(MrhsArgs A) {
             if (!live[j]) continue;
             const MrhsSys &S = A.s[q * G + j];
             if (MODE == M_DHAT) {
-                // the centre, and the reduction's operand beside it (the centre
-                // itself when aux is the centre)
+                // the centre, and the reduction's operand beside it
                 const Spinor<R> cen = SpinorIO<P>::template load<true>(S.center, Vh, i);
                 Spinor<R> ax;
-                if (RED != R_NONE) ax = (S.aux == S.center) ? cen : SpinorIO<P>::template load<true>(S.aux, Vh, i);
+                if (RED != R_NONE) ax = SpinorIO<P>::template load<true>(S.aux, Vh, i);
 #pragma unroll
                 for (int k = 0; k < 12; k++) acc[j].c[k] = cen.c[k] + coef * acc[j].c[k];
                 SpinorIO<P>::template store<false>(S.out, Vh, i, acc[j]);
-                if (RED != R_NONE) {
-#pragma unroll
-                    for (int k = 0; k < 12; k++) {
-                        const double ar = ax.c[k].re, ai = ax.c[k].im, orr = acc[j].c[k].re, oi = acc[j].c[k].im;
-                        red[j][0] += ar * orr + ai * oi;
-                        red[j][1] += ar * oi - ai * orr;
-                        if (NR == 3) red[j][NR - 1] += orr * orr + oi * oi;
-                    }
+                if (RED == R_DOT) red_add<true, false, 12>(red[j], ax.c, acc[j].c);
+                if (RED == R_STEP) {
+                    red_add<true, true, 12>(red[j], cen.c, acc[j].c);
+                    red_add<true, false, 12>(red[j] + 3, ax.c, acc[j].c);
                 }
             } else {
                 SpinorIO<P>::template store<false>(S.out, Vh, i, acc[j]);
@@ -757,7 +779,7 @@ template <int P, int MODE, int RED> void launch_mrhs_mode(const MrhsArgs &A, int
 template <int P> void dispatch_mrhs(const MrhsArgs &A, int mode, int red, int blocks, hipStream_t s, int lr, int G) {
     if (mode == M_HOPINV) launch_mrhs_mode<P, M_HOPINV, R_NONE>(A, blocks, s, lr, G);
     else if (red == R_DOT) launch_mrhs_mode<P, M_DHAT, R_DOT>(A, blocks, s, lr, G);
-    else if (red == R_DOTNORM) launch_mrhs_mode<P, M_DHAT, R_DOTNORM>(A, blocks, s, lr, G);
+    else if (red == R_STEP) launch_mrhs_mode<P, M_DHAT, R_STEP>(A, blocks, s, lr, G);
     else launch_mrhs_mode<P, M_DHAT, R_NONE>(A, blocks, s, lr, G);
 }
 
@@ -790,8 +812,6 @@ struct PersistArgs {
     unsigned long long epoch; // written to the abort word when a wait runs out
     long long limit;          // wall-clock ticks a wait may take
 };
-
-__device__ __forceinline__ int rho_slot_p(int iter) { return (iter & 1) ? S_RHO1 : S_RHO0; }
 
 // from this many blocks up the kernel's own barrier beats the runtime's
 constexpr int kOwnBarrierMinBlocks = 16;
@@ -860,37 +880,6 @@ template <bool OWN> __device__ __forceinline__ bool grid_barrier(const PersistAr
     }
     __syncthreads();
     return ok;
-}
-
-// a value every lane holds alike, read from lane 0 so the compiler knows it
-// is uniform (branches on it stay scalar, pointers chosen by it stay in SGPRs)
-__device__ __forceinline__ double uniform(double v) {
-    const long long b = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_readfirstlane((int)(b & 0xffffffff));
-    const int hi = __builtin_amdgcn_readfirstlane((int)(b >> 32));
-    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-
-// every block: the N sums of the partials, in the finalize kernel's order
-template <int N> __device__ __forceinline__ void sum_partials(const double *part, int nblk, double (&out)[N]) {
-    __shared__ double sh[N][kWaves];
-    __shared__ double tot[N];
-    double a[N];
-#pragma unroll
-    for (int k = 0; k < N; k++) a[k] = 0.0;
-    for (int j = threadIdx.x; j < nblk; j += kBlock) {
-#pragma unroll
-        for (int k = 0; k < N; k++) a[k] += part[(size_t)k * nblk + j];
-    }
-    block_fold<N>(a, sh);
-    if (threadIdx.x == 0) {
-#pragma unroll
-        for (int k = 0; k < N; k++) tot[k] = a[k];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < N; k++) out[k] = uniform(tot[k]);
-    __syncthreads();
 }
 
 // out = F^-1 H in (one parity), the MULT of the launched path
@@ -997,7 +986,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(P == P64
         }
         if (!second) {
             double sm[2];
-            sum_partials<2>(A.part[0], A.nblk, sm);
+            sum_partials<2, 0>(SumSource{A.part[0], A.nblk}, SumSource{nullptr, 0}, sm);
             const cx<double> rq = {sm[0], sm[1]};
             al = cdiv(rho, rq);
             // s = r - alpha q (in r) with ||s||^2; the half-step check
@@ -1016,7 +1005,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(P == P64
                 timed_out = true;
                 break;
             }
-            sum_partials<1>(A.part[1], A.nblk, n);
+            sum_partials<1, 0>(SumSource{A.part[1], A.nblk}, SumSource{nullptr, 0}, n);
             if (threadIdx.x == 0) {
                 kept[K_RQ] = rq.re;
                 kept[K_RQ + 1] = rq.im;
@@ -1036,7 +1025,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(P == P64
             continue;
         }
         double sm[3];
-        sum_partials<3>(A.part[0], A.nblk, sm);
+        sum_partials<3, 0>(SumSource{A.part[0], A.nblk}, SumSource{nullptr, 0}, sm);
         const cx<double> st = {sm[0], sm[1]};
         const double tt = sm[2];
         // x += alpha p + omega s; r = s - omega t with ||r||^2, <r~, r>
@@ -1071,7 +1060,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(P == P64
             timed_out = true;
             break;
         }
-        sum_partials<3>(A.part[1], A.nblk, v3);
+        sum_partials<3, 0>(SumSource{A.part[1], A.nblk}, SumSource{nullptr, 0}, v3);
         const double rr = v3[0];
         const cx<double> rho1 = {v3[1], v3[2]};
         if (threadIdx.x == 0) {
@@ -1085,12 +1074,6 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(P == P64
         if (bad || rr < tol2) {
             done = (rr < tol2) ? DONE_FULL : DONE_BREAK;
             stopph = 2;
-            // the scalars of a full step, as the launched path leaves them
-            if (lb == 0 && threadIdx.x == 0) {
-                const int nxt = rho_slot_p(it + 1);
-                A.sc[nxt] = rho1.re;
-                A.sc[nxt + 1] = rho1.im;
-            }
             it++;
             break;
         }
@@ -1116,14 +1099,12 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(P == P64
         done = DONE_BREAK;
         stopph = 3;
     }
-    // leave the scalars and flags as the launched path would
+    // leave the flags as the launched path would, and the scalars the host's
+    // closing update reads
     if (lb == 0 && threadIdx.x == 0) {
         double *sc = A.sc;
-        if (stopph != 2) {
-            const int cur = rho_slot_p(it);
-            sc[cur] = rho.re;
-            sc[cur + 1] = rho.im;
-        }
+        sc[S_RHO1] = rho.re;  // with S_RQ, the alpha of a half-step exit
+        sc[S_RHO1 + 1] = rho.im;
         sc[S_RQ] = kept[K_RQ];
         sc[S_RQ + 1] = kept[K_RQ + 1];
         sc[S_SS] = kept[K_SS];
@@ -1161,7 +1142,7 @@ static int launch_mult_mrhs(hipStream_t s, const MultCall *calls, int n, wc_latt
         const MultCall &c = calls[k];
         if (c.coef != c0.coef) return wc_fail(WC_EINVAL, "multi-system stencil calls must share the coefficient");
         A.s[k] = MrhsSys{c.out, c.in, c.center, c.aux, c.red_to.partials, c.done};
-        bytes += mult_spinor_bytes(c.prec, c.mode, c.red, c.aux == c.center, lat->Vh);
+        bytes += mult_spinor_bytes(c.prec, c.mode, c.red, lat->Vh);
         lat->dslash_count++;
     }
     if (A.ngroups > kMrhsMaxGroups) return wc_fail(WC_EINVAL, "too many systems per multi-system launch");
@@ -1175,8 +1156,7 @@ static int launch_mult_mrhs(hipStream_t s, const MultCall *calls, int n, wc_latt
         TimedPart op{{}, mult_operator_bytes(c0.prec, c0.mode, lr, lat->Vh)};
         for (int k = 0; k < n; k++) {
             const MultCall &c = calls[k];
-            t.parts.push_back(TimedPart{{c.done}, mult_spinor_bytes(c.prec, c.mode, c.red, c.aux == c.center,
-                                                                      lat->Vh)});
+            t.parts.push_back(TimedPart{{c.done}, mult_spinor_bytes(c.prec, c.mode, c.red, lat->Vh)});
             op.owners.push_back(c.done);
         }
         t.parts.push_back(op);
@@ -1185,7 +1165,7 @@ static int launch_mult_mrhs(hipStream_t s, const MultCall *calls, int n, wc_latt
     else dispatch_mrhs<P16>(A, c0.mode, c0.red, blocks, s, 12, G);
     WC_HIP(hipGetLastError());
     if (tl->timing) timing_end(tl, t);
-    if (c0.red != R_NONE) {
+    if (c0.red != R_NONE && c0.red_to.result) {
         FinArgs f[kMaxSys];
         for (int k = 0; k < n; k++) {
             f[k] = FinArgs{};
@@ -1195,31 +1175,43 @@ static int launch_mult_mrhs(hipStream_t s, const MultCall *calls, int n, wc_latt
             f[k].result = calls[k].red_to.result;
             f[k].guard = calls[k].done;
         }
-        return launch_fin_batch(s, f, n, c0.red == R_DOT ? 2 : 3);
+        return launch_fin_batch(s, f, n, red_values(c0.red));
     }
     return WC_OK;
+}
+
+// the form that a launch of these calls takes
+enum StencilForm { F_PLAIN, F_SPLIT, F_MULTI };
+static StencilForm stencil_form(const MultCall *calls, int n) {
+    const MultCall &c0 = calls[0];
+    // several systems on one lattice in an inner-precision stencil: the
+    // multi-system form, when the lattice has it switched on
+    bool same = n > 1 && mrhs_for(c0.lat, c0.prec) > 0 && (c0.prec == P32 || c0.prec == P16) &&
+                (c0.mode == M_HOPINV || c0.mode == M_DHAT);
+    for (int k = 1; same && k < n; k++)
+        same = calls[k].lat == c0.lat && calls[k].prec == c0.prec && calls[k].mode == c0.mode &&
+               calls[k].red == c0.red && calls[k].out_par == c0.out_par && calls[k].coef == c0.coef;
+    if (same) return F_MULTI;
+    // systems interleaved on one lattice share the operator through the cache,
+    // which the split form's non-temporal loads would undo
+    bool split = c0.mode != M_CLOV;
+    for (int k = 0; split && k < n; k++)
+        split = split_stencil(calls[k].lat, c0.prec) && (k == 0 || calls[k].lat != c0.lat);
+    return split ? F_SPLIT : F_PLAIN;
+}
+
+int stencil_partials(const MultCall *calls, int n, int k) {
+    return blocks_of(calls[k].lat->Vh, stencil_form(calls, n) == F_PLAIN ? launch_bs(calls[0].bs) : 64);
 }
 
 int launch_mult_batch(hipStream_t s, const MultCall *calls, int n, wc_lattice *timing_lat) {
     if (n <= 0) return WC_OK;
     if (n > kMaxSys) return wc_fail(WC_EINVAL, "too many systems in one batch");
     const MultCall &c0 = calls[0];
-    {
-        // several systems on one lattice in an inner-precision stencil: the
-        // multi-system form, when the lattice has it switched on
-        bool same = n > 1 && mrhs_for(c0.lat, c0.prec) > 0 && (c0.prec == P32 || c0.prec == P16) &&
-                    (c0.mode == M_HOPINV || c0.mode == M_DHAT);
-        for (int k = 1; same && k < n; k++)
-            same = calls[k].lat == c0.lat && calls[k].prec == c0.prec && calls[k].mode == c0.mode &&
-                   calls[k].red == c0.red && calls[k].out_par == c0.out_par && calls[k].coef == c0.coef;
-        if (same) return launch_mult_mrhs(s, calls, n, timing_lat ? timing_lat : c0.lat, mrhs_for(c0.lat, c0.prec));
-    }
+    const StencilForm form = stencil_form(calls, n);
+    if (form == F_MULTI) return launch_mult_mrhs(s, calls, n, timing_lat ? timing_lat : c0.lat, mrhs_for(c0.lat, c0.prec));
     if (!valid_block_size(launch_bs(c0.bs))) return wc_fail(WC_EINVAL, "block size must be 64, 128 or 256");
-    bool split = true;
-    // (systems interleaved on one lattice share the operator through the cache,
-    // which the split form's non-temporal loads would undo)
-    for (int k = 0; k < n; k++)
-        split = split && c0.mode != M_CLOV && split_stencil(calls[k].lat, c0.prec) && (k == 0 || calls[k].lat != c0.lat);
+    const bool split = form == F_SPLIT;
     const int bs = split ? 64 : launch_bs(c0.bs);  // sites per workgroup
     MultBatch B;
     B.h.S = n;
@@ -1254,7 +1246,7 @@ int launch_mult_batch(hipStream_t s, const MultCall *calls, int n, wc_lattice *t
         a.done = c.done;
         a.nblk = blocks_of(lat->Vh, bs);
         B.h.off[k + 1] = B.h.off[k] + a.nblk;
-        bytes += mult_spinor_bytes(c.prec, c.mode, c.red, c.aux == c.center, lat->Vh);
+        bytes += mult_spinor_bytes(c.prec, c.mode, c.red, lat->Vh);
         bool seen = false;
         for (int j = 0; j < k; j++) seen = seen || (calls[j].lat == lat);
         if (!seen) bytes += mult_operator_bytes(c.prec, c.mode, lr, lat->Vh);
@@ -1280,8 +1272,7 @@ int launch_mult_batch(hipStream_t s, const MultCall *calls, int n, wc_lattice *t
         t.phase = tl->tag_phase;
         for (int k = 0; k < n; k++) {
             const MultCall &c = calls[k];
-            t.parts.push_back(TimedPart{{c.done}, mult_spinor_bytes(c.prec, c.mode, c.red, c.aux == c.center,
-                                                                      c.lat->Vh)});
+            t.parts.push_back(TimedPart{{c.done}, mult_spinor_bytes(c.prec, c.mode, c.red, c.lat->Vh)});
             bool seen = false;
             for (int j = 0; j < k; j++) seen = seen || (calls[j].lat == c.lat);
             if (seen) continue;
@@ -1298,7 +1289,7 @@ int launch_mult_batch(hipStream_t s, const MultCall *calls, int n, wc_lattice *t
     else dispatch_mode<P16>(B, c0.mode, c0.red, blocks, shape, lds, s, 12);
     WC_HIP(hipGetLastError());
     if (tl->timing) timing_end(tl, t);
-    if (c0.red != R_NONE && c0.mode == M_DHAT) {
+    if (c0.red != R_NONE && c0.mode == M_DHAT && c0.red_to.result) {
         FinArgs f[kMaxSys];
         for (int k = 0; k < n; k++) {
             f[k] = FinArgs{};
@@ -1308,7 +1299,7 @@ int launch_mult_batch(hipStream_t s, const MultCall *calls, int n, wc_lattice *t
             f[k].result = calls[k].red_to.result;
             f[k].guard = calls[k].done;
         }
-        return launch_fin_batch(s, f, n, c0.red == R_DOT ? 2 : 3);
+        return launch_fin_batch(s, f, n, red_values(c0.red));
     }
     return WC_OK;
 }

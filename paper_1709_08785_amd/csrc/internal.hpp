@@ -23,15 +23,19 @@ enum ScalarSlot {
     S_ST = 3,      // <s, t>             (complex)
     S_TT = 5,      // ||t||^2
     S_RR = 6,      // ||r||^2
-    S_RHO0 = 7,    // rho, slot 0        (complex)
-    S_RHO1 = 9,    // rho, slot 1        (complex)
+    // rho: the outer loop alternates between the two slots; in the inner loop
+    // S_RHO0 is the rho of the coming iteration and S_RHO1 that of the running
+    // one, so that no kernel reads a slot it also writes
+    S_RHO0 = 7,    // (complex)
+    S_RHO1 = 9,    // (complex)
     // the pipelined inner loop keeps its coefficients in fixed slots:
     //   alpha in S_RQ, omega in S_ST, beta in S_RHO1, rho = <r~, r> in S_RHO0,
     //   <r~, s> and <r~, z> in S_AUX and S_AUX + 2, ||q||^2 in S_SS, ||y||^2 in S_TT
     S_NORM = 11,   // ||p||^2 of the inner call's source (Algorithm 2, first step)
     S_AUX = 12,    // scratch norms (4 doubles)
     S_TOL2 = 16,   // squared relative tolerance of the running inner loop
-    S_COUNT = 20
+    S_FOLD = 20,   // folded sums of the inner loop's next update (8 doubles)
+    S_COUNT = 28
 };
 // flags block (ints): done code, iterations completed
 // F_STOPPH: where the inner loop stopped: 1 at the half-step check (after the
@@ -42,7 +46,11 @@ enum DoneCode { DONE_NO = 0, DONE_FULL = 1, DONE_HALF = 2, DONE_BREAK = 4 };
 
 enum { NUM_LEVELS = 2 };  // 0 = inner loop, 1 = outer / FP64 loop
 constexpr int kMaxSys = 16;  // systems per batched launch
-constexpr int kMaxRed = 8;   // values one fused reduction may carry (partials are sized for it)
+constexpr int kMaxRed = 8;   // values one fused reduction may carry
+// a system's reduction partials, in units of its 64-site tiles: a reduction
+// that is summed by its finalize kernel uses the first kMaxRed; the inner loop
+// keeps its four reductions apart, each until the update that consumes it
+enum PartialSlot { PS_STEP = 0, PS_RQ = 5, PS_RR = 7, PS_SS = 8, PS_COUNT = 11 };
 // block sizes the solver's per-site kernels may run with (64-site tiles per
 // block: 1, 2 or 4); reduction partials are sized for the smallest
 constexpr int kMinBlock = 64;
@@ -95,7 +103,7 @@ struct TimedLaunch {
 struct SysState {
     double *scalars = nullptr;     // [NUM_LEVELS][S_COUNT]
     int *flags = nullptr;          // [NUM_LEVELS][F_COUNT]
-    double *partials = nullptr;    // [kMaxRed][blocks]: room for the 64-thread block count of the lattice
+    double *partials = nullptr;    // [PS_COUNT][tiles]: room for the 64-thread block count of the lattice
     size_t partials_bytes = 0;
     double *partials2 = nullptr;   // a second set, for the one-launch inner loop (single-system state only)
     unsigned long long *bar = nullptr;  // its grid barrier: [blocks] arrivals, release, abort (zeroed once)
@@ -298,14 +306,18 @@ void timing_settle(wc_lattice *lat, size_t from, const std::vector<StopPoint> &s
 // ---------------------------------------------------------------------------
 struct RedTarget {
     double *partials;
-    double *result;  // final sums written here (FIN_STORE)
+    double *result;  // final sums written here (FIN_STORE); null: the caller's next kernel sums the partials
+};
+// partials [k][n] that a kernel sums before it starts
+struct SumSource {
+    const double *p;
+    int n;
 };
 
 enum FinOp {
     FIN_STORE = 0,   // result[0..n) = sums
     FIN_INIT,        // rho0 = (sum, 0); reset the level's done flag and iteration count
-    FIN_INNER_A,     // ||s||^2; done = HALF below tol2, BREAK on a non-finite alpha or sum
-    FIN_INNER_B,     // ||r||^2, rho1 = <r~, r>, iterations = iter + 1; done = FULL / BREAK
+    FIN_CHECK,       // ||r||^2 of the inner loop's last iteration: done = FULL / BREAK
     FIN_OUTER_B,     // ||r||^2, rho1 = <r~, r>
     FIN_PIPE_INIT,   // alpha = rho / <r~, w>, beta = 0, omega = 1 (no partials)
     FIN_PIPE_A,      // omega = <y, q> / ||y||^2; <r~, s>, <r~, z>; done = HALF on ||q||^2 < tol2
@@ -324,8 +336,15 @@ struct FinArgs {
     int iter;
     double tol2;
 };
-// one block per system; nvals values per system (1..3)
+// one block per system; nvals values per system
 int launch_fin_batch(hipStream_t s, const FinArgs *f, int n, int nvals);
+// out[0..na) and out[na..na+nb) = the sums of each system's two sources
+struct FoldArgs {
+    SumSource a, b;
+    double *out;
+    const int *guard;
+};
+int launch_fold_batch(hipStream_t s, const FoldArgs *f, int n, int na, int nb);
 
 // ---------------------------------------------------------------------------
 // stencil launches (dslash.hip).  A batch is a list of calls with the same
@@ -334,7 +353,9 @@ int launch_fin_batch(hipStream_t s, const FinArgs *f, int n, int nvals);
 // blocks that read the same links and clover run together on one XCD.
 // ---------------------------------------------------------------------------
 enum MultMode { M_HOPINV = 0, M_DHAT = 1, M_DFULL = 2, M_INVSRC = 3, M_CLOV = 4 };
-enum MultRed { R_NONE = 0, R_DOT = 1, R_DOTNORM = 2 };
+// R_DOT <aux, out>; R_DOTNORM and ||out||^2; R_STEP <center, out>, ||out||^2, <aux, out>
+enum MultRed { R_NONE = 0, R_DOT = 1, R_DOTNORM = 2, R_STEP = 3 };
+__host__ __device__ constexpr int red_values(int red) { return red == R_DOT ? 2 : red == R_DOTNORM ? 3 : red == R_STEP ? 5 : 0; }
 
 // The FP64 stencil is held to 2 workgroups of 256 threads (8 waves) per CU: its
 // L2 then keeps more of the neighbours that the resident waves share.  (With
@@ -398,6 +419,8 @@ struct MultCall {
 };
 // timing_lat (default: the first call's lattice) receives the timing record
 int launch_mult_batch(hipStream_t s, const MultCall *calls, int n, wc_lattice *timing_lat = nullptr);
+// partials per value that such a launch leaves for calls[k]
+int stencil_partials(const MultCall *calls, int n, int k);
 // one call on lat; a call without a block size takes the lattice's
 inline int launch_mult(wc_lattice *lat, MultCall c) {
     c.lat = lat;
@@ -433,13 +456,13 @@ enum VecOp {
     V_SUB_NORM,     // a = b - c (FP64)                   -> result[0] = ||a||^2
     V_AXPY,         // a += coef b (FP64)
     V_INNER_INIT,   // a: src (FP64), b: r, c: r~, d: p, e: x   (Algorithm 2 set-up)
-    V_INNER_A,      // a: r, b: q                         r -= alpha q
-    V_INNER_B,      // a: x, b: r, c: p, d: t, e: r~      x += alpha p + omega s, r = s - omega t
-    V_INNER_C,      // a: p, b: r, c: q                   p = r + beta (p - omega q)
+    V_INNER_A,      // a: r, b: q, c: r~                  r -= alpha q
+    V_INNER_B,      // a: x, b: r, c: p, d: t, e: q       x += alpha p + omega s, r = s - omega t, p = r + beta (p - omega q)
     V_INNER_FIX,    // a: x, b: p                         x += alpha p
     V_INNER_FINAL,  // a: v (FP64), b: x                  v = ||src|| x
     V_OUTER_A,      // a: x, b: r, c: v, d: q             x += alpha v, r -= alpha q
     V_OUTER_B,      // a: x, b: r, c: v, d: t, e: r~      x += omega v, r -= omega t
+    V_OUTER_C,      // a: p, b: r, c: q                   p = r + beta (p - omega q)
     V_GAMMA5,       // a: FP64 two-parity field, in place
     V_COPY,         // a = b (FP64 single parity)
     V_ZERO,         // a = 0 (FP64 single parity)
@@ -457,11 +480,11 @@ struct VecCall {
     int *fl;           // flag block of the system's level
     double *partials;
     double *result;    // V_NORM2 / V_SUB_NORM destination
+    SumSource in0, in1;  // V_INNER_A: <r~, q>, the last ||r||^2; V_INNER_B: the second D-hat's sums, ||s||^2 and <r~, s>
     double tol2;
     double coef;
-    int iter;          // iteration index, when not taken from the device
+    int iter;          // iteration index (outer loop)
     int guard;         // skip when fl[F_DONE] != 0
-    int iter_dev;      // take the iteration index from fl[F_ITERS] (inner loop)
     int bs;            // threads per block of the launch (64, 128 or 256; 0 = 256)
 };
 // prec: storage precision of the inner vectors (the inner solution x is FP64

@@ -1,7 +1,7 @@
 // Deterministic two-stage reductions for 64-wide wavefronts.
 //
 // Stage 1 (inside the producing kernel): each block folds its per-thread
-// values with a wave shuffle tree and an LDS pass in a fixed order and writes
+// values over its wavefronts and an LDS pass in a fixed order and writes
 // one partial per value with a plain store.  Stage 2 is a separate one-block
 // kernel (k_finalize, blas.hip) that sums the partials in block order and runs
 // the scalar logic of the solver.  The kernel boundary makes the partials
@@ -16,11 +16,39 @@
 constexpr int kBlock = 256;
 constexpr int kWaves = kBlock / 64;
 
+// one step of the wave fold: the lanes that dpp control CTRL supplies with a
+// neighbour's value add it, the rows not in ROWS add zero
+template <int CTRL, int ROWS> __device__ __forceinline__ double dpp_add(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xffffffff), CTRL, ROWS, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, ROWS, 0xf, true);
+    return v + __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
+// Sum over the wavefront, in every lane.  Rows of 16 lanes by shifts, then the
+// rows by broadcasts of lanes 15 and 31; the total arrives in lane 63.  These
+// are moves between registers: as shuffles the 12 exchanges of each value went
+// through LDS, and the split stencil, with four wavefronts on 64 sites, spent
+// 25 us of a 192 us D-hat half at 32^3x64 on them.
 template <int N> __device__ __forceinline__ void wave_fold(double (&v)[N]) {
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
+    for (int k = 0; k < N; k++) v[k] = dpp_add<0x111, 0xf>(v[k]);  // row_shr:1
 #pragma unroll
-        for (int k = 0; k < N; k++) v[k] += __shfl_down(v[k], off, 64);
+    for (int k = 0; k < N; k++) v[k] = dpp_add<0x112, 0xf>(v[k]);  // row_shr:2
+#pragma unroll
+    for (int k = 0; k < N; k++) v[k] = dpp_add<0x114, 0xf>(v[k]);  // row_shr:4
+#pragma unroll
+    for (int k = 0; k < N; k++) v[k] = dpp_add<0x118, 0xf>(v[k]);  // row_shr:8
+#pragma unroll
+    for (int k = 0; k < N; k++) v[k] = dpp_add<0x142, 0xa>(v[k]);  // row_bcast:15
+#pragma unroll
+    for (int k = 0; k < N; k++) v[k] = dpp_add<0x143, 0xc>(v[k]);  // row_bcast:31
+#pragma unroll
+    for (int k = 0; k < N; k++) {
+        const long long b = __double_as_longlong(v[k]);
+        const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffff), 63);
+        const int hi = __builtin_amdgcn_readlane((int)(b >> 32), 63);
+        v[k] = __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
     }
 }
 
@@ -55,6 +83,50 @@ __device__ __forceinline__ void block_partials(double (&v)[N], double *partials,
 #pragma unroll
         for (int k = 0; k < N; k++) partials[(size_t)k * G + blk] = v[k];
     }
+}
+
+// a value every lane holds alike, read from lane 0 so the compiler knows it
+// is uniform (branches on it stay scalar, pointers chosen by it stay in SGPRs)
+__device__ __forceinline__ double uniform(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readfirstlane((int)(b & 0xffffffff));
+    const int hi = __builtin_amdgcn_readfirstlane((int)(b >> 32));
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
+// Every block: the NA + NB sums of two sets of partials, in one order for all
+// blocks.  Every thread of the block must call this.
+template <int NA, int NB>
+__device__ __forceinline__ void sum_partials(SumSource a, SumSource b, double (&out)[NA + NB]) {
+    constexpr int N = NA + NB;
+    __shared__ double sh[N][kWaves];
+    double v[N];
+#pragma unroll
+    for (int k = 0; k < N; k++) v[k] = 0.0;
+#pragma unroll 4
+    for (int j = threadIdx.x; j < a.n; j += blockDim.x) {
+#pragma unroll
+        for (int k = 0; k < NA; k++) v[k] += a.p[(size_t)k * a.n + j];
+    }
+#pragma unroll 4
+    for (int j = threadIdx.x; j < b.n; j += blockDim.x) {
+#pragma unroll
+        for (int k = 0; k < NB; k++) v[NA + k] += b.p[(size_t)k * b.n + j];
+    }
+    wave_fold<N>(v);
+    if ((threadIdx.x & 63) == 0) {
+#pragma unroll
+        for (int k = 0; k < N; k++) sh[k][threadIdx.x >> 6] = v[k];
+    }
+    __syncthreads();
+    const int nw = blockDim.x >> 6;
+#pragma unroll
+    for (int k = 0; k < N; k++) {
+        double s = 0.0;
+        for (int w = 0; w < nw; w++) s += sh[k][w];
+        out[k] = uniform(s);
+    }
+    __syncthreads();
 }
 
 // A batched launch covers several systems.  Concatenated: system s owns the

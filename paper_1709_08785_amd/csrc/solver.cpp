@@ -156,7 +156,6 @@ VecCall vc9(Run &R, int k, int lvl, void *a, void *b, void *c, void *d, void *e,
 int inner_chunk_pipe(Run &R, const std::vector<int> &act, int n, int base = 0) {
     const int L = 0, P = R.iprec;
     auto loop = [&](VecCall v) {
-        v.iter_dev = 1;
         v.guard = 1;
         return v;
     };
@@ -185,41 +184,124 @@ int inner_chunk_pipe(Run &R, const std::vector<int> &act, int n, int base = 0) {
     return WC_OK;
 }
 
+// the four reductions of an inner iteration, apart from each other (PartialSlot)
+double *partials(Run &R, int k, int slot) {
+    return S_(R, k).st->partials + (size_t)slot * blocks_of(S_(R, k).lat->Vh, kMinBlock);
+}
+
+// From this many partials of one value on, a fold kernel sums them once instead
+// of every block of the next update.  The update's blocks each read all of them:
+// at 1024 (16^3x32) that is 40 KB a block and costs less than a launch, at
+// 5184 (24^3x48) it is 200 KB in each of 1296 blocks.
+constexpr int kFoldPartials = 1280;
+
+// the sources that the update after a reduction sums: the stencil's na values
+// (`stencil`) and the previous update's nb (`vec`), folded into the
+// scalar block first where some system has too many partials
+int inner_sources(Run &R, const std::vector<int> &act, int stencil, int na, int vec, int nb, const int *ns,
+                  SumSource *in0, SumSource *in1) {
+    bool fold = false;
+    FoldArgs f[kMaxSys];
+    int n = 0;
+    for (int k : act) {
+        in0[n] = SumSource{partials(R, k, stencil), ns[n]};
+        in1[n] = SumSource{partials(R, k, vec), blocks_of(S_(R, k).lat->Vh, R.bs)};
+        fold = fold || in0[n].n >= kFoldPartials || in1[n].n >= kFoldPartials;
+        n++;
+    }
+    if (!fold) return WC_OK;
+    n = 0;
+    for (int k : act) {
+        double *out = S_(R, k).st->sc(0) + S_FOLD;
+        f[n] = FoldArgs{in0[n], in1[n], out, S_(R, k).st->fl(0) + F_DONE};
+        in0[n] = SumSource{out, 1};
+        in1[n] = SumSource{out + na, 1};
+        n++;
+    }
+    return launch_fold_batch(R.stream, f, n, na, nb);
+}
+
+// D-hat of the inner loop with its sums (with r~ among them) left as partials,
+// ns[] of them per value
+int inner_dhat(Run &R, const std::vector<int> &act, int out_id, int in_id, int red, int slot, int *ns) {
+    const int L = 0, P = R.iprec;
+    if (int rc = mult_over(R, act, [&](int k) {
+            MultCall c = mc(R, k, P, M_HOPINV, 1, W(R, k, W_ITMP), W(R, k, in_id), nullptr, 0.0);
+            c.done = S_(R, k).st->fl(L);
+            return c;
+        }))
+        return rc;
+    MultCall calls[kMaxSys];
+    int n = 0;
+    for (int k : act) {
+        SolveSys &s = S_(R, k);
+        MultCall c = mc(R, k, P, M_DHAT, 0, W(R, k, out_id), W(R, k, W_ITMP), W(R, k, in_id),
+                        -s.lat->kappa * s.lat->kappa);
+        c.red = red;
+        c.aux = W(R, k, W_IRT);
+        c.red_to = RedTarget{partials(R, k, slot), nullptr};
+        c.done = s.st->fl(L);
+        calls[n++] = c;
+        R.dslash[k]++;
+    }
+    for (int j = 0; j < n; j++) ns[j] = stencil_partials(calls, n, j);
+    return launch_mult_batch(R.stream, calls, n, R.tl);
+}
+
 // one chunk of n iterations of Algorithm 2 for the systems in act; every
-// kernel takes the iteration index from the system's device flags, so the
-// same launches serve any chunk (and can be recorded once as a graph)
+// kernel takes its coefficients from the device, so the same launches serve
+// any chunk (and can be recorded once as a graph)
 int inner_chunk(Run &R, const std::vector<int> &act, int n, int base = 0) {
     const int L = 0, P = R.iprec;
-    auto loop = [&](VecCall v) {
-        v.iter_dev = 1;
+    int ns[kMaxSys];
+    SumSource in0[kMaxSys], in1[kMaxSys];
+    // an update with its sources and the slot of its own sum
+    auto update = [&](int j, int slot, VecCall v) {
         v.guard = 1;
+        v.in0 = in0[j];
+        v.in1 = in1[j];
+        v.partials = partials(R, act[j], slot);
         return v;
     };
     // tags for the timing records: iteration and phase (0: first D-hat and the
-    // s update, 1: second D-hat and the x, r update, 2: the p update)
+    // s update, 1: second D-hat and the x, r, p update)
     auto tag = [&](int it, int ph) {
         R.tl->tag_iter = it;
         R.tl->tag_phase = ph;
     };
     for (int j = 0; j < n; j++) {
         tag(base + j, 0);
-        if (int rc = dhat(R, act, P, W_IQ, W_IP, W_ITMP, R_DOT, W_IRT, L, S_RQ, true)) return rc;
+        if (int rc = inner_dhat(R, act, W_IQ, W_IP, R_DOT, PS_RQ, ns)) return rc;
+        if (int rc = inner_sources(R, act, PS_RQ, 2, PS_RR, 1, ns, in0, in1)) return rc;
+        int i = 0;
         if (int rc = vec_over(R, act, V_INNER_A, P,
-                              [&](int k) { return loop(vc(R, k, L, W(R, k, W_IR), W(R, k, W_IQ))); }))
+                              [&](int k) { return update(i++, PS_SS, vc(R, k, L, W(R, k, W_IR), W(R, k, W_IQ), W(R, k, W_IRT))); }))
             return rc;
         tag(base + j, 1);
-        if (int rc = dhat(R, act, P, W_IT, W_IR, W_ITMP, R_DOTNORM, W_IR, L, S_ST, true)) return rc;
+        if (int rc = inner_dhat(R, act, W_IT, W_IR, R_STEP, PS_STEP, ns)) return rc;
+        if (int rc = inner_sources(R, act, PS_STEP, 5, PS_SS, 3, ns, in0, in1)) return rc;
+        i = 0;
         if (int rc = vec_over(R, act, V_INNER_B, P, [&](int k) {
-                return loop(vc(R, k, L, W(R, k, W_IX), W(R, k, W_IR), W(R, k, W_IP), W(R, k, W_IT), W(R, k, W_IRT)));
+                return update(i++, PS_RR, vc(R, k, L, W(R, k, W_IX), W(R, k, W_IR), W(R, k, W_IP), W(R, k, W_IT),
+                                             W(R, k, W_IQ)));
             }))
-            return rc;
-        tag(base + j, 2);
-        if (int rc = vec_over(R, act, V_INNER_C, P,
-                              [&](int k) { return loop(vc(R, k, L, W(R, k, W_IP), W(R, k, W_IR), W(R, k, W_IQ))); }))
             return rc;
     }
     tag(-1, 0);
-    return WC_OK;
+    // the last iteration's test, before the host reads the flags
+    FinArgs f[kMaxSys];
+    int nf = 0;
+    for (int k : act) {
+        FinArgs a = FinArgs{};
+        a.op = FIN_CHECK;
+        a.blocks = blocks_of(S_(R, k).lat->Vh, R.bs);
+        a.partials = partials(R, k, PS_RR);
+        a.sc = S_(R, k).st->sc(L);
+        a.fl = S_(R, k).st->fl(L);
+        a.guard = a.fl;
+        f[nf++] = a;
+    }
+    return launch_fin_batch(R.stream, f, nf, 1);
 }
 
 // run a chunk through a graph recorded once per (systems, precision, length,
@@ -395,9 +477,7 @@ int inner_solve(Run &R, const std::vector<int> &act, int src_id, int v_id) {
     }
     if (!fix.empty())
         if (int rc = vec_over(R, fix, R.pipe ? V_PIPE_FIX : V_INNER_FIX, P, [&](int k) {
-                VecCall v = vc(R, k, L, W(R, k, W_IX), W(R, k, W_IP));
-                v.iter = S_(R, k).st->hf(L, F_ITERS);
-                return v;
+                return vc(R, k, L, W(R, k, W_IX), W(R, k, W_IP));
             }))
             return rc;
     return vec_over(R, act, V_INNER_FINAL, P, [&](int k) { return vc(R, k, L, W(R, k, v_id), W(R, k, W_IX)); });
@@ -526,7 +606,7 @@ int outer_flexible(Run &R, std::vector<int> act, bool x_is_zero) {
         }
         prune(R, act);
         if (act.empty()) break;
-        if (int rc = vec_over(R, act, V_INNER_C, P64, [&](int k) {
+        if (int rc = vec_over(R, act, V_OUTER_C, P64, [&](int k) {
                 VecCall v = vc(R, k, L, W(R, k, W_P), W(R, k, W_R), W(R, k, W_Q));
                 v.iter = it;
                 return v;
