@@ -171,13 +171,14 @@ int wc_tune_block_size(wc_lattice *lat, int prec, double us_per_pair[3], int *th
    wc_solve_multi that share a lattice): many solutions per gauge field (Sec.
    II-A) apply the same operator, so the inner loop's MULTs (F^-1 H of eq. 9 and
    the second half of D-hat_ee, eq. 8) of all systems on one lattice run in one
-   launch in which each thread takes one site for systems_per_thread systems:
-   it computes the neighbour indices and rebuilds each link once, loads each
-   clover block once, and applies them to every system's spinors.
+   launch that reads and rebuilds each link and loads each clover block once for
+   all of them: a workgroup takes one 64-site tile and goes through the systems
+   with the operator in registers.  A few FP16 systems (fewer than 6 on a lattice
+   of more than 1024 tiles) are taken systems_per_thread at a time by each thread.
    wc_set_multi_rhs: systems_per_thread = 2 or 4, 0 for one system per thread
    (each system's sites in workgroups of their own, the operator shared through
-   the cache), or -1 (default) for 2 in FP32 and 4 in FP16, the faster setting
-   of each precision on the 12-source batch.  WC_EINVAL for other values.
+   the cache), or -1 (default) for 2 in FP32 and 4 in FP16.  WC_EINVAL for other
+   values.
    Results agree with single solves to rounding.  wc_multi_rhs: systems per
    thread a batch in precision prec uses now (0 for FP64, which has no
    multi-system form), or -1 for a null lattice or bad precision. */
@@ -324,8 +325,8 @@ int wc_apply_Dee_oo(wc_lattice *lat, void *out_e, const void *in_e, int prec);
    on this lattice, out[k] = MULT in[k] (eq. 9) resp. out_e[k] = D-hat_ee in_e[k]
    (eq. 8), in one launch per MULT (many solutions per gauge field, Sec. II-A).
    With the multi-system stencil on (wc_set_multi_rhs) and prec WC_FP32 or
-   WC_FP16, each thread applies one site's links and clover blocks to several
-   of the fields; otherwise the fields' workgroups are interleaved.  Arguments
+   WC_FP16, each site's links and clover blocks are loaded once and applied to
+   all the fields; otherwise the fields' workgroups are interleaved.  Arguments
    as for the single forms; out, in (out_e, in_e) are host arrays of n device
    pointers.  The D-hat_ee form keeps n single-parity temporaries of the
    precision in the lattice until it is destroyed. */

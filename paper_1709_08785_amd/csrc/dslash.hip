@@ -577,16 +577,32 @@ double mult_operator_bytes(int prec, int mode, int lr, int Vh) {
 
 // ---------------------------------------------------------------------------
 // Several right-hand sides on one lattice (many solutions per gauge field,
-// Sec. II-A): one thread takes one output site for G systems at once.  The
-// neighbour indices, each link (with its third column rebuilt) and each
-// clover block are computed or loaded once and applied to all G spinors, so
-// the per-site work that does not depend on the source is shared, and the
-// operator is read from memory once per site for every system of the launch.
-// A wavefront covers the 64 sites of one tile for one group of G systems, and
-// the waves of all groups of a tile form one workgroup (so they run on one
-// compute unit), so their link and clover loads after the first hit in cache.
-// Reductions are per wave: each wave folds its G systems' sums and writes one
-// partial per system and tile, which the finalize stage sums in tile order.
+// Sec. II-A), in two forms.
+//
+// k_mult_multi: a workgroup of two wavefronts takes a 64-site tile (or, where
+// tiles alone would leave compute units idle, a tile and some of the systems)
+// and goes through its systems one after the other.  Wavefront 0 holds the links
+// of the x and y hops, wavefront 1 those of z and t, each also one chiral clover
+// block: the operator is read and rebuilt once for all systems and stays in
+// registers.  Per system the two exchange half sums through LDS, apply their
+// block and store one half of the spinor.  Many fields are bound by what the L2
+// must fetch: their neighbourhoods do not fit it together.  Here a workgroup has
+// one system in flight, all workgroups of an XCD go through the systems in step,
+// and the L2 holds one system's neighbourhood at a time: for 12 fields at
+// 32^3x64 it fetches 3.5 GB a MULT, where one wavefront per pair of systems
+// fetched 4.5.  The four neighbours are loaded plane by plane, so that those
+// along x and y find each other's lines in L1 (24% fewer L2 requests).  FP32,
+// us before -> now, MULT | D-hat_ee: 12 fields 16^3x32 72 -> 53 | 160 -> 116,
+// 24^3x48 351 -> 295 | 746 -> 622, 32^3x64 1012 -> 846 | 2178 -> 1786; 2 fields
+// 32^3x64 314 -> 231 | 657 -> 490.  Loading the next system's neighbours ahead,
+// with the clover blocks in LDS, was slower: 895 us for the 32^3x64 MULT, since
+// two systems in flight fetch 5.0 GB.
+//
+// k_mult_mrhs: one thread takes one output site for G systems at once and applies
+// each link and clover block, loaded once, to all G.  A wavefront covers the 64
+// sites of one tile for one group of G systems, the waves of all groups of a tile
+// form one workgroup.  It remains for a few FP16 fields on large lattices
+// (multi_by_tile).
 // ---------------------------------------------------------------------------
 struct MrhsSys {
     void *out;
@@ -605,9 +621,9 @@ struct MrhsArgs {
     const void *clov;
     double coef;
     int nsys;     // systems of the launch
-    int ngroups;  // groups of G systems: ceil(nsys / G)
+    int ngroups;  // groups of systems (k_mult_mrhs: of G systems, ceil(nsys / G))
     int ntiles;   // 64-site tiles of one parity
-    int chunk;    // tiles per XCD chunk of the block remap (0: one slab per XCD)
+    int chunk;    // workgroups per XCD chunk of the block remap (0: one slab per XCD)
     MrhsSys s[kMaxSys];
 };
 
@@ -758,29 +774,284 @@ __global__ __launch_bounds__(64 * kMrhsMaxGroups) void k_mult_mrhs(MrhsArgs A) {
     }
 }
 
-template <int P, int MODE, int RED, int LR, int G>
-void launch_mrhs_g(const MrhsArgs &A, int blocks, hipStream_t s) {
-    hipLaunchKernelGGL((k_mult_mrhs<P, MODE, RED, LR, G>), dim3(blocks), dim3(64 * A.ngroups), 0, s, A);
+// both links of direction MU at a site, and the two neighbours
+template <int P, int MU, int LR>
+__device__ __forceinline__ void load_dir(const MrhsArgs &A, const SiteCoord &c, int i, Mat3<typename Real<P>::T> *U,
+                                         int *n) {
+    const int Vh = A.g.Vh;
+    n[0] = eo_neighbour(A.g, c, MU, +1);
+    n[1] = eo_neighbour(A.g, c, MU, -1);
+    U[0] = LinkLoad<P, LR>::template load<true>(A.links + (size_t)(2 * MU + A.out_par) * A.link_slab, Vh, i);
+    U[1] = LinkLoad<P, LR>::template load<true>(A.links + (size_t)(2 * MU + 1 - A.out_par) * A.link_slab, Vh, n[1]);
 }
 
-template <int P, int MODE, int RED, int LR> void launch_mrhs_lr(const MrhsArgs &A, int blocks, hipStream_t s, int G) {
-    if (G == 2) launch_mrhs_g<P, MODE, RED, LR, 2>(A, blocks, s);
-    else launch_mrhs_g<P, MODE, RED, LR, 4>(A, blocks, s);
-}
-
-template <int P, int MODE, int RED> void launch_mrhs_mode(const MrhsArgs &A, int blocks, hipStream_t s, int lr, int G) {
-    if constexpr (P == P32) {
-        if (lr == 8) return launch_mrhs_lr<P, MODE, RED, 8>(A, blocks, s, G);
-        if (lr == 18) return launch_mrhs_lr<P, MODE, RED, 18>(A, blocks, s, G);
+// a neighbour's spinor as it is stored
+template <int P> struct RawSpinor {
+    float4 v[6];
+};
+template <> struct RawSpinor<P16> {
+    uint4 v[3];
+    float s;
+};
+// four neighbours, plane by plane: those along x and y lie in the same lines
+template <int P> __device__ __forceinline__ void raw_load4(RawSpinor<P> (&r)[4], const void *in, const int (&n)[4]) {
+    if constexpr (P == P16) {
+#pragma unroll
+        for (int k = 0; k < 3; k++)
+#pragma unroll
+            for (int j = 0; j < 4; j++) r[j].v[k] = *tp<uint4, 52>(in, n[j], 16 * k);
+#pragma unroll
+        for (int j = 0; j < 4; j++) r[j].s = *tp<float, 52>(in, n[j], 48);
+    } else {
+#pragma unroll
+        for (int k = 0; k < 6; k++)
+#pragma unroll
+            for (int j = 0; j < 4; j++) r[j].v[k] = *tp<float4, 96>(in, n[j], 16 * k);
     }
-    launch_mrhs_lr<P, MODE, RED, 12>(A, blocks, s, G);
+}
+template <int P, int MU, bool FWD>
+__device__ __forceinline__ void raw_hop(const RawSpinor<P> &r, const Mat3<float> &U, Spinor<float> &acc) {
+    if constexpr (P == P16) {
+        hop_term<float, MU, FWD, true>(SpinorIO<P16>::decode(r.v), U, acc, r.s);
+    } else {
+        Spinor<float> p;
+#pragma unroll
+        for (int k = 0; k < 6; k++) {
+            p.c[2 * k] = {r.v[k].x, r.v[k].y};
+            p.c[2 * k + 1] = {r.v[k].z, r.v[k].w};
+        }
+        hop_term<float, MU, FWD, false>(p, U, acc, 1.0f);
+    }
 }
 
-template <int P> void dispatch_mrhs(const MrhsArgs &A, int mode, int red, int blocks, hipStream_t s, int lr, int G) {
-    if (mode == M_HOPINV) launch_mrhs_mode<P, M_HOPINV, R_NONE>(A, blocks, s, lr, G);
-    else if (red == R_DOT) launch_mrhs_mode<P, M_DHAT, R_DOT>(A, blocks, s, lr, G);
-    else if (red == R_STEP) launch_mrhs_mode<P, M_DHAT, R_STEP>(A, blocks, s, lr, G);
-    else launch_mrhs_mode<P, M_DHAT, R_NONE>(A, blocks, s, lr, G);
+constexpr int kMultiWaves = 2;
+
+// a clover block put away in LDS, and read back
+__device__ __forceinline__ void park(float4 (*p)[64], int lane, const Herm6<float> &M) {
+    p[0][lane] = make_float4(M.d[0], M.d[1], M.d[2], M.d[3]);
+    p[1][lane] = make_float4(M.d[4], M.d[5], M.o[0].re, M.o[0].im);
+#pragma unroll
+    for (int k = 0; k < 7; k++)
+        p[2 + k][lane] = make_float4(M.o[1 + 2 * k].re, M.o[1 + 2 * k].im, M.o[2 + 2 * k].re, M.o[2 + 2 * k].im);
+}
+__device__ __forceinline__ Herm6<float> unpark(const float4 (*p)[64], int lane) {
+    Herm6<float> M;
+    const float4 a = p[0][lane], b = p[1][lane];
+    M.d[0] = a.x;
+    M.d[1] = a.y;
+    M.d[2] = a.z;
+    M.d[3] = a.w;
+    M.d[4] = b.x;
+    M.d[5] = b.y;
+    M.o[0] = {b.z, b.w};
+#pragma unroll
+    for (int k = 0; k < 7; k++) {
+        const float4 f = p[2 + k][lane];
+        M.o[1 + 2 * k] = {f.x, f.y};
+        M.o[2 + 2 * k] = {f.z, f.w};
+    }
+    return M;
+}
+
+// Two wavefronts per SIMD: a wavefront keeps 72 registers of links, 36 of clover
+// block and four neighbours in flight.
+template <int P, int MODE, int RED, int LR>
+__global__ __launch_bounds__(64 * kMultiWaves) __attribute__((amdgpu_waves_per_eu(2))) void k_mult_multi(MrhsArgs A) {
+    using R = typename Real<P>::T;
+    constexpr int NR = RED == R_NONE ? 1 : red_values(RED);
+    __shared__ cx<R> xch[2][6][64], ych[2][6][64];
+    __shared__ float mx[2][64];
+    __shared__ double rs[2][kMaxSys][NR];
+    // with a reduction the registers do not hold the clover block as well: it
+    // waits in LDS between the systems
+    constexpr bool kParkM = P == P32 && RED != R_NONE;
+    __shared__ float4 parked[2][kParkM ? 9 : 1][64];
+    const int L = xcd_block(blockIdx.x, gridDim.x, A.chunk);
+    const int tile = L / A.ngroups, grp = L - tile * A.ngroups;
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+    // the systems of this group that still run
+    const int s0 = grp * A.nsys / A.ngroups, s1 = (grp + 1) * A.nsys / A.ngroups;
+    unsigned live = 0;
+    {
+        // (every flag is read before the first is looked at)
+        int flag[kMaxSys];
+#pragma unroll
+        for (int s = 0; s < kMaxSys; s++) {
+            const int *d = A.s[s < A.nsys ? s : 0].done;
+            flag[s] = *(d ? d : (const int *)A.links);
+        }
+#pragma unroll
+        for (int s = 0; s < kMaxSys; s++)
+            if (s >= s0 && s < s1 && !(A.s[s].done && flag[s])) live |= 1u << s;
+    }
+    if (!live) return;
+    const int Vh = A.g.Vh;
+    const int i = tile * 64 + lane;
+    const bool active = i < Vh;
+    Herm6<R> M;
+    Mat3<R> U[4];
+    int n[4] = {0, 0, 0, 0};
+    R cs = R(1);
+    if (active) {
+        const SiteCoord c = eo_coords(A.g, i, A.out_par);
+        if (w == 0) {
+            load_dir<P, 0, LR>(A, c, i, U, n);
+            load_dir<P, 1, LR>(A, c, i, U + 2, n + 2);
+        } else {
+            load_dir<P, 2, LR>(A, c, i, U, n);
+            load_dir<P, 3, LR>(A, c, i, U + 2, n + 2);
+        }
+        if constexpr (P == P16) {
+            M = CloverIO<P16>::template load_scaled<true>(A.clov, Vh, i, w, 1.0f);
+            cs = CloverIO<P16>::scale(A.clov, i);
+        } else {
+            M = CloverIO<P>::template load<true>(A.clov, Vh, i, w);
+        }
+    }
+    if constexpr (kParkM) {
+        if (active) park(parked[w], lane, M);
+    }
+    const R coef = (R)A.coef;
+    for (unsigned todo = live; todo;) {
+        const int s = __builtin_ctz(todo);
+        todo &= todo - 1;
+        const MrhsSys &S = A.s[s];
+        cx<R> cen[6], ax[6], v[6], out[6];
+        if (active) {
+            Spinor<R> acc;
+#pragma unroll
+            for (int k = 0; k < 12; k++) acc.c[k] = {R(0), R(0)};
+            RawSpinor<P> psi[4];
+            raw_load4<P>(psi, S.in, n);
+            if (w == 0) {
+                raw_hop<P, 0, true>(psi[0], U[0], acc);
+                raw_hop<P, 0, false>(psi[1], U[1], acc);
+                raw_hop<P, 1, true>(psi[2], U[2], acc);
+                raw_hop<P, 1, false>(psi[3], U[3], acc);
+            } else {
+                raw_hop<P, 2, true>(psi[0], U[0], acc);
+                raw_hop<P, 2, false>(psi[1], U[1], acc);
+                raw_hop<P, 3, true>(psi[2], U[2], acc);
+                raw_hop<P, 3, false>(psi[3], U[3], acc);
+            }
+            if constexpr (MODE == M_DHAT) {
+                half_load<P, true>(S.center, i, w, cen);
+                if constexpr (RED != R_NONE) half_load<P, true>(S.aux, i, w, ax);
+            }
+#pragma unroll
+            for (int k = 0; k < 6; k++) {
+                const cx<R> m = acc.c[k] - acc.c[k + 6], q = acc.c[k] + acc.c[k + 6];
+                v[k] = w ? q : m;
+                xch[w][k][lane] = w ? m : q;
+            }
+        }
+        __syncthreads();
+        if (active) {
+            cx<R> y[6];
+#pragma unroll
+            for (int k = 0; k < 6; k++) v[k] = v[k] + xch[1 - w][k][lane];
+            if constexpr (kParkM) M = unpark(parked[w], lane);
+            herm6_apply(M, v, y);
+#pragma unroll
+            for (int k = 0; k < 6; k++) {
+                v[k] = y[k];
+                ych[w][k][lane] = y[k];
+            }
+        }
+        __syncthreads();
+        if (active) {
+#pragma unroll
+            for (int k = 0; k < 6; k++) {
+                const cx<R> o = ych[1 - w][k][lane];
+                cx<R> t = w ? v[k] - o : o + v[k];  // yp - ym, yp + ym
+                if (P == P16) t = cs * t;
+                if (MODE == M_DHAT) t = cen[k] + coef * t;
+                out[k] = t;
+            }
+        }
+        float m = 0.f;
+        if constexpr (P == P16) {
+            if (active) {
+#pragma unroll
+                for (int k = 0; k < 6; k++) m = fmaxf(m, fmaxf(fabsf(out[k].re), fabsf(out[k].im)));
+                mx[w][lane] = m;
+            }
+            __syncthreads();
+            if (active) m = fmaxf(m, mx[1 - w][lane]);
+        }
+        if (active) half_store<P>(S.out, i, w, out, m);
+        if constexpr (RED != R_NONE) {
+            double r[NR];
+#pragma unroll
+            for (int k = 0; k < NR; k++) r[k] = 0.0;
+            if (active) {
+#pragma unroll
+                for (int k = 0; k < 6; k++) {
+                    keep(cen[k]);
+                    keep(ax[k]);
+                }
+                if (RED == R_STEP) {
+                    red_add<true, true, 6>(r, cen, out);
+                    red_add<true, false, 6>(r + 3, ax, out);
+                } else {
+                    red_add<true, false, 6>(r, ax, out);
+                }
+            }
+            wave_fold<NR>(r);
+            if (lane == 0) {
+#pragma unroll
+                for (int k = 0; k < NR; k++) rs[w][s][k] = r[k];
+            }
+        }
+    }
+    if constexpr (RED != R_NONE) {
+        __syncthreads();
+        for (int t = threadIdx.x; t < kMaxSys * NR; t += 64 * kMultiWaves) {
+            const int s = t / NR, k = t - s * NR;
+            if (live >> s & 1) A.s[s].partials[(size_t)k * A.ntiles + tile] = rs[0][s][k] + rs[1][s][k];
+        }
+    }
+}
+
+// Which form a launch takes.  k_mult_multi, except for FP16 storage with fewer
+// than 6 fields on more than 1024 tiles: a field's bytes are half as many there,
+// so fewer fields' neighbourhoods fit the L2, and k_mult_mrhs has more
+// wavefronts in flight (D-hat_ee, k_mult_mrhs -> k_mult_multi, us: 2 fields
+// 24^3x48 107 -> 138, 32^3x64 324 -> 392, but 16^3x32 36 -> 33; 6 fields 24^3x48
+// 294 -> 285; a 12-source solve at 8^4 9.1 -> 5.1 ms, at 20^3x32 69 -> 65).
+bool multi_by_tile(int prec, int ntiles, int nsys) { return prec == P32 || nsys >= 6 || ntiles <= kSplitTiles; }
+
+template <int P, int MODE, int RED, int LR> void launch_mrhs_lr(const MrhsArgs &A, hipStream_t s, int G) {
+    if (multi_by_tile(P, A.ntiles, A.nsys)) {
+        MrhsArgs B = A;
+        // four workgroups fit a compute unit: fill them once, whole systems each
+        // (two rounds of half as many systems: 16^3x32, 12 fields 50 -> 65 us)
+        B.ngroups = std::max(1, std::min(A.nsys, 1024 / A.ntiles));
+        B.chunk = A.chunk * B.ngroups;
+        hipLaunchKernelGGL((k_mult_multi<P, MODE, RED, LR>), dim3(A.ntiles * B.ngroups), dim3(64 * kMultiWaves), 0, s, B);
+        return;
+    }
+    if constexpr (P == P16) {
+        MrhsArgs B = A;
+        B.ngroups = (A.nsys + G - 1) / G;
+        if (G == 2) hipLaunchKernelGGL((k_mult_mrhs<P, MODE, RED, LR, 2>), dim3(A.ntiles), dim3(64 * B.ngroups), 0, s, B);
+        else hipLaunchKernelGGL((k_mult_mrhs<P, MODE, RED, LR, 4>), dim3(A.ntiles), dim3(64 * B.ngroups), 0, s, B);
+    }
+}
+
+template <int P, int MODE, int RED> void launch_mrhs_mode(const MrhsArgs &A, hipStream_t s, int lr, int G) {
+    if constexpr (P == P32) {
+        if (lr == 8) return launch_mrhs_lr<P, MODE, RED, 8>(A, s, G);
+        if (lr == 18) return launch_mrhs_lr<P, MODE, RED, 18>(A, s, G);
+    }
+    launch_mrhs_lr<P, MODE, RED, 12>(A, s, G);
+}
+
+template <int P> void dispatch_mrhs(const MrhsArgs &A, int mode, int red, hipStream_t s, int lr, int G) {
+    if (mode == M_HOPINV) launch_mrhs_mode<P, M_HOPINV, R_NONE>(A, s, lr, G);
+    else if (red == R_DOT) launch_mrhs_mode<P, M_DHAT, R_DOT>(A, s, lr, G);
+    else if (red == R_STEP) launch_mrhs_mode<P, M_DHAT, R_STEP>(A, s, lr, G);
+    else launch_mrhs_mode<P, M_DHAT, R_NONE>(A, s, lr, G);
 }
 
 // ---------------------------------------------------------------------------
@@ -1134,7 +1405,7 @@ static int launch_mult_mrhs(hipStream_t s, const MultCall *calls, int n, wc_latt
     A.clov = (const char *)lat->clovinv[c0.prec] + (size_t)c0.out_par * clover_slab_bytes(c0.prec, lat->Vh);
     A.coef = c0.coef;
     A.nsys = n;
-    A.ngroups = (n + G - 1) / G;
+    A.ngroups = 0;  // set with the form
     A.ntiles = blocks_of(lat->Vh, 64);
     A.chunk = lattice_chunk(lat, c0.prec);
     double bytes = mult_operator_bytes(c0.prec, c0.mode, lr, lat->Vh);
@@ -1145,8 +1416,6 @@ static int launch_mult_mrhs(hipStream_t s, const MultCall *calls, int n, wc_latt
         bytes += mult_spinor_bytes(c.prec, c.mode, c.red, lat->Vh);
         lat->dslash_count++;
     }
-    if (A.ngroups > kMrhsMaxGroups) return wc_fail(WC_EINVAL, "too many systems per multi-system launch");
-    const int blocks = A.ntiles;
     int slot = c0.mode == M_HOPINV ? KS_MULT_HOPINV_P64 + c0.prec : KS_MULT_DHAT_P64 + c0.prec;
     TimedLaunch t;
     if (tl->timing) {
@@ -1161,8 +1430,8 @@ static int launch_mult_mrhs(hipStream_t s, const MultCall *calls, int n, wc_latt
         }
         t.parts.push_back(op);
     }
-    if (c0.prec == P32) dispatch_mrhs<P32>(A, c0.mode, c0.red, blocks, s, lr, G);
-    else dispatch_mrhs<P16>(A, c0.mode, c0.red, blocks, s, 12, G);
+    if (c0.prec == P32) dispatch_mrhs<P32>(A, c0.mode, c0.red, s, lr, G);
+    else dispatch_mrhs<P16>(A, c0.mode, c0.red, s, 12, G);
     WC_HIP(hipGetLastError());
     if (tl->timing) timing_end(tl, t);
     if (c0.red != R_NONE && c0.red_to.result) {
