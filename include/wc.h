@@ -137,8 +137,12 @@ void wc_solve_params_default(wc_solve_params *p);
    loop tiling of Sec. III-B).  Sites are stored in tiles of 64 (one tile per
    wavefront); a workgroup covers 1, 2 or 4 tiles, i.e. 64, 128 or 256
    threads.  Small lattices fill more compute units with small workgroups;
-   large ones prefer large.  Unless pinned, the size is tuned per inner
-   precision on the first solve of a lattice (wc_tune_block_size) and reused.
+   large ones prefer large.  Unless pinned, the size is chosen per inner
+   precision on the first solve of a lattice and reused: by timing
+   (wc_tune_block_size) where the stencil runs one thread per site (FP16
+   storage and reconstruct-8 links above 1024 tiles), else by a rule on the
+   lattice's size, since there the stencil gives every 64-site tile four
+   wavefronts whatever the block size and only the vector kernels use it.
    Results do not depend on it beyond the rounding order of the reductions.
 
    wc_set_block_size: threads = 64, 128 or 256 pins the size for every
@@ -149,7 +153,8 @@ void wc_solve_params_default(wc_solve_params *p);
    odd parity, then the D-hat half with its fused dot; Sec. II-B eq. 8) on
    zero vectors at 64, 128 and 256 threads and at XCD chunks of 8, 16, 32 and
    64 tiles (wc_set_xcd_chunk; only the pinned one when pinned) and keeps the
-   fastest shape; 256 threads at chunk 32 are displaced only by a shape at
+   fastest shape; 256 threads (64 on lattices of up to 256 tiles, where the
+   stencil does not depend on it) at chunk 32 are displaced only by a shape at
    least 3% faster, in the sweep and again in three alternating timings
    against it.  With a pinned block size, the chunk and caps are chosen
    for that size.  At that shape it then times the two kernels on their
@@ -190,8 +195,9 @@ int wc_multi_rhs(const wc_lattice *lat, int prec);
    library remaps them so that each XCD takes chunks of `tiles` consecutive
    64-site tiles, the XCDs sweeping the lattice side by side (neighbours in y
    and z then fall in the XCD's own chunk).  tiles = 0 gives each XCD one
-   contiguous slab instead.  Unless pinned, the chunk is tuned with the block
-   size (wc_tune_block_size); before tuning it is 32.  Results do not depend
+   contiguous slab instead.  Unless pinned, the chunk is chosen with the block
+   size (64 tiles by rule on lattices of up to 1024 tiles, else 32); before
+   that it is 32.  Results do not depend
    on it.  wc_set_xcd_chunk: tiles in [0, 2^20] pins it for every precision,
    -1 returns to tuning; WC_EINVAL otherwise.  wc_xcd_chunk: the chunk a
    launch in precision prec uses now (-2 for a null lattice or bad prec). */
@@ -203,12 +209,12 @@ int wc_xcd_chunk(const wc_lattice *lat, int prec);
    wavefronts of such a launch in precision prec share a compute unit.  The
    library applies it by reserving LDS that the kernels do not use, so results
    do not depend on it.  A cap that keeps fewer waves resident lets the L2
-   keep more of the neighbour spinors those waves share: the FP64 stencil runs
-   10-11% faster at 8 waves per CU than at the 12 its registers allow.
+   keep more of the neighbour spinors those waves share.
    Unless pinned, the cap is chosen per precision and per kernel class (the
    D-hat half, and every other stencil) by the launch-shape tuner
    (wc_tune_block_size) among no cap, 8 and 12 waves; before tuning it is 8
-   for FP64 and none for FP32 and FP16.
+   for FP64 and none for FP32 and FP16, and where the stencil gives each tile
+   four wavefronts (wc_set_block_size) it stays so.
    wc_set_wave_cap: 4, 8, 12 or 16 waves pins the cap of both classes, 0 pins
    no cap, -1 returns to tuning.  Changing it drops the tuned launch shape of
    that precision.  WC_EINVAL for other values or a bad precision.  Batches of

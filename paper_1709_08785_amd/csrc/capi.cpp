@@ -798,6 +798,41 @@ static void tune_store(const std::string &key, int bs, int chunk, const int caps
     std::fclose(f);
 }
 
+// take the stored shape of a case, if the cache file has it
+static bool stored_shape(wc_lattice *lat, int prec, const std::string &key, double us[3]) {
+    int b = 0, c = -1, w[2] = {-1, -1};
+    if (!tune_lookup(key, &b, &c, w, us)) return false;
+    lat->bs_tuned[prec] = b;
+    lat->chunk_tuned[prec] = c;
+    // a file may hold caps that were timed on another form of the stencil
+    const bool split = split_stencil(lat, prec);
+    for (int k = 0; k < 2; k++) lat->cap_tuned[prec][k] = split ? default_wave_cap(prec) : w[k];
+    lat->gen++;
+    return true;
+}
+
+// The vector kernels' block size where the split stencil leaves it to them: 64
+// threads while that gives every compute unit at most one block (FP64
+// 12x14x10x18: 67.3 us an inner iteration against 69.2 at 256), 256 above
+// (16^4: 69.7 against 75.9 at 64).
+static int split_block_size(const wc_lattice *lat) { return pad_sites(lat->Vh) / kTile <= 256 ? 64 : 256; }
+
+// The launch shape of a lattice's first solve.  For the split stencil it follows
+// from the lattice: no wave cap gained anything at any size from 8^4 to 48^3x96
+// (FP32 at 8 and 12 waves per CU loses 1-25%, FP64 fits 8 anyway), and chunks of
+// 16 and 32 tiles lie within 1%, with 64 up to 4% ahead at 16^4 and 16^3x32, whose
+// XCDs then sweep one or two stretches each.  Timing that would cost the first
+// solve 10-25 ms.  The one-thread-per-site stencil is timed.
+int first_shape(wc_lattice *lat, int prec) {
+    if (!split_stencil(lat, prec)) return tune_block_size(lat, prec, nullptr, nullptr);
+    double us[3];
+    if (!lat->bs_pin && lat->chunk_pin < 0 && stored_shape(lat, prec, tune_key(lat, prec), us)) return WC_OK;
+    lat->bs_tuned[prec] = lat->bs_pin ? lat->bs_pin : split_block_size(lat);
+    lat->chunk_tuned[prec] = pad_sites(lat->Vh) / kTile <= 1024 ? 64 : kDefaultChunk;
+    lat->gen++;  // captured graphs hold the old launch shape
+    return WC_OK;
+}
+
 // Time the inner loop's stencil pair (F_oo^-1 H_oe into the odd parity, then
 // the D-hat half with its fused dot) on zero vectors at each block size and
 // XCD chunk, and keep the fastest.  The default shape (256 threads, chunk
@@ -817,18 +852,12 @@ int tune_block_size(wc_lattice *lat, int prec, double us[3], int *chosen) {
         return wc_fail(WC_ENOTREADY, "block-size tuning needs links and clover");
     const std::string key = tune_key(lat, prec);
     const bool use_cache = !lat->bs_pin && lat->chunk_pin < 0;
-    if (use_cache) {
-        int b = 0, c = -1, w[2] = {-1, -1};
+    {
         double u[3];
-        if (tune_lookup(key, &b, &c, w, u)) {
-            lat->bs_tuned[prec] = b;
-            lat->chunk_tuned[prec] = c;
-            lat->cap_tuned[prec][0] = w[0];
-            lat->cap_tuned[prec][1] = w[1];
-            lat->gen++;
+        if (use_cache && stored_shape(lat, prec, key, u)) {
             if (us)
                 for (int k = 0; k < 3; k++) us[k] = u[k];
-            if (chosen) *chosen = b;
+            if (chosen) *chosen = lat->bs_tuned[prec];
             return WC_OK;
         }
     }
@@ -886,20 +915,19 @@ int tune_block_size(wc_lattice *lat, int prec, double us[3], int *chosen) {
             rc = wc_fail(WC_EHIP, "block-size tuning: setting up buffers and events");
             break;
         }
-        // about 2 ms of pairs per candidate, between 4 and 64
+        // about 1 ms of pairs per candidate, between 4 and 64
         double ms = 0;
         lat->chunk_force = chunks[0];
         if ((rc = timed(256, 2, &ms))) break;
-        const int reps = std::max(4, std::min(64, (int)(2.0 / std::max(ms, 1e-3))));
+        const int reps = std::max(4, std::min(64, (int)(1.0 / std::max(ms, 1e-3))));
         // start from 256 threads (or the pinned size) at the first chunk;
         // another shape must win by 3%.  A pinned block size is the only one
         // the choice of chunk and caps considers.
         const int pin = lat->bs_pin;
         // The split stencil has one block size, so one timing serves all three
-        // and the size is that of the vector kernels alone: 64 while that still
-        // gives every compute unit at most one block, 256 above.
+        // and the size is that of the vector kernels alone.
         const bool split = split_stencil(lat, prec);
-        const int bs0 = pin ? pin : (split && pad_sites(lat->Vh) / kTile <= 256) ? 64 : 256;
+        const int bs0 = pin ? pin : split ? split_block_size(lat) : 256;
         const size_t start = bs0 == 64 ? 0 : bs0 == 128 ? 1 : 2;
         for (size_t h = 0; h < chunks.size() && !rc; h++) {
             lat->chunk_force = chunks[h];
@@ -911,7 +939,7 @@ int tune_block_size(wc_lattice *lat, int prec, double us[3], int *chosen) {
         best = start;
         for (size_t k = 0; k < t.size(); k++)
             if (((!pin && !split) || k % 3 == start) && t[k] < 0.97 * t[best]) best = k;
-        // One timing of about 2 ms can favour a shape by a few percent by
+        // One timing of about 1 ms can favour a shape by a few percent by
         // chance, so a challenger is timed again against the starting shape,
         // alternately, three times each, and keeps its place only if the
         // better of its times still wins by 3%.
@@ -941,8 +969,9 @@ int tune_block_size(wc_lattice *lat, int prec, double us[3], int *chosen) {
             if (rc) break;
             if (!wins) best = start;
         }
-        // the wave cap of each kernel class at that shape
-        if (lat->wave_cap[prec] >= 0 || lat->lds_per_cu <= 0) break;
+        // the wave cap of each kernel class at that shape (the split stencil
+        // gains from none: first_shape)
+        if (split || lat->wave_cap[prec] >= 0 || lat->lds_per_cu <= 0) break;
         lat->chunk_force = chunks[best / 3];
         const int bsb = cand[best % 3];
         const int def = default_wave_cap(prec);

@@ -430,6 +430,8 @@ inline int launch_mult(wc_lattice *lat, MultCall c) {
 // time the stencil pair of the inner loop at each block size and keep the
 // fastest for (lat, prec) (capi.cpp); us[3] and chosen may be null
 int tune_block_size(wc_lattice *lat, int prec, double us[3], int *chosen);
+// the shape for the first solve of (lat, prec): by rule, from the cache file or tuned
+int first_shape(wc_lattice *lat, int prec);
 
 // the inner loop of one system as a single cooperative launch (dslash.hip)
 struct PersistCall {

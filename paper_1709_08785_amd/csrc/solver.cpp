@@ -734,14 +734,14 @@ int solve_systems(std::vector<SolveSys> &sys, Arena &arena, double tol, const wc
     R.pipe = P.inner_method == WC_INNER_PIPELINED;
     R.persistent = P.persistent != 0;
     // block size: each lattice's pinned or tuned value for the inner
-    // precision (tuned now if neither); a batch over several lattices runs
+    // precision (chosen now if neither); a batch over several lattices runs
     // with the largest lattice's, which dominates its cost
     {
         wc_lattice *big = sys[0].lat;
         for (auto &s : sys) {
             if ((!s.lat->bs_pin && !s.lat->bs_tuned[P.inner_prec]) ||
                 (s.lat->chunk_pin < 0 && s.lat->chunk_tuned[P.inner_prec] < 0)) {
-                const int rc = tune_block_size(s.lat, P.inner_prec, nullptr, nullptr);
+                const int rc = first_shape(s.lat, P.inner_prec);
                 if (rc == WC_ENOMEM) {  // no room to time: the defaults
                     s.lat->bs_tuned[P.inner_prec] = 256;
                     s.lat->chunk_tuned[P.inner_prec] = kDefaultChunk;
