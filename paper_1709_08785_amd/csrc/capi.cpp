@@ -86,9 +86,7 @@ void arena_bind(Arena &a, int k, SysState &st) {
 }
 
 int sync_arena(const Arena &a, hipStream_t s) {
-    WC_HIP(hipMemcpyAsync(a.h_scalars, a.scalars, sizeof(double) * NUM_LEVELS * S_COUNT * a.S, hipMemcpyDeviceToHost,
-                          s));
-    WC_HIP(hipMemcpyAsync(a.h_flags, a.flags, sizeof(int) * NUM_LEVELS * F_COUNT * a.S, hipMemcpyDeviceToHost, s));
+    if (int rc = launch_publish(a, s)) return rc;
     WC_HIP(hipStreamSynchronize(s));
     return WC_OK;
 }

@@ -286,6 +286,7 @@ int arena_alloc(Arena &a, int S, hipStream_t s);
 void arena_free(Arena &a);
 void arena_bind(Arena &a, int k, SysState &st);
 int sync_arena(const Arena &a, hipStream_t s);
+int launch_publish(const Arena &a, hipStream_t s);  // the arena into its pinned mirrors (blas.hip)
 
 // ---------------------------------------------------------------------------
 // timing hooks around launches
