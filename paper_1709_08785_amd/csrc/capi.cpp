@@ -1105,13 +1105,22 @@ extern "C" int wc_apply_D(wc_lattice *lat, void *out_dev, const void *in_dev, in
     const size_t sb = spinor_bytes(prec, lat->Vh);
     void *in2, *out2;
     if (int rc = lwork(lat, LW_APPLY_IN, 2 * sb, &in2)) return rc;
-    if (int rc = lwork(lat, LW_APPLY_OUT, 2 * sb, &out2)) return rc;
+    const bool canon = split_stencil(lat, prec);
+    if (!canon)
+        if (int rc = lwork(lat, LW_APPLY_OUT, 2 * sb, &out2)) return rc;
     if (int rc = launch_pack_spinor(lat, prec, in2, in_dev)) return rc;
+    MultCall c[2];
     for (int par = 0; par < 2; par++) {
-        MultCall c = mult_call(prec, M_DFULL, par, (char *)out2 + par * sb, (const char *)in2 + (1 - par) * sb,
-                               (const char *)in2 + par * sb, -lat->kappa);
-        if (int rc = launch_mult(lat, c)) return rc;
+        c[par] = mult_call(prec, canon ? M_DCANON : M_DFULL, par, canon ? out_dev : (char *)out2 + par * sb,
+                           (const char *)in2 + (1 - par) * sb, (const char *)in2 + par * sb, -lat->kappa);
+        c[par].lat = lat;
+        c[par].bs = lattice_bs(lat, prec);
     }
+    // the split stencil takes both parities in one launch, which share the
+    // links, and writes the canonical layout itself
+    if (canon) return launch_mult_batch(lat->stream, c, 2);
+    for (int par = 0; par < 2; par++)
+        if (int rc = launch_mult_batch(lat->stream, &c[par], 1)) return rc;
     return launch_unpack_spinor(lat, prec, out_dev, out2);
 }
 

@@ -307,6 +307,14 @@ void k_mult(MultBatch B) {
 // 266 -> 242, 48^3x96 4029 -> 3891; FP32 24^3x48 119 -> 107 (5.7 TB/s), 32^3x64
 // 326 -> 315, 48^3x96 1843 -> 1772; full links 141 -> 128, 397 -> 384, 2151 ->
 // 2112.  Which lattices take it: split_stencil.
+//
+// D on canonical fields (M_DCANON) moves memory too, and its two parities read
+// the same links: as two launches and an unpack it fetched them twice and the
+// result made a round trip through the tiled layout.  One launch with the
+// parities' tiles interleaved meets the links in L2 and writes the result where
+// the caller wants it.  The whole call, pack included, us: FP64 8^4 20 -> 14,
+// 20x12x28x36 140 -> 99, 32^3x64 1140 -> 825; FP32 82 -> 63, 638 -> 540 at the
+// larger two.
 // ---------------------------------------------------------------------------
 constexpr int kSplitWaves = 4;
 constexpr int kSplitBlock = -64;  // "block size" that selects it: 64 sites per workgroup
@@ -372,7 +380,7 @@ __device__ __forceinline__ void half_store(void *base, int i, int h, const cx<ty
 // Held to the waves per SIMD that the loads of a direction leave registers for
 // (the reductions alone would cost the FP32 D-hat half its fourth wave).
 template <int P, int MODE, int LR> constexpr int split_waves() {
-    return P == P64 ? 2 : (LR == 8 || MODE == M_DFULL || MODE == M_INVSRC) ? 3 : 4;
+    return P == P64 ? 2 : (LR == 8 || MODE == M_DFULL || MODE == M_DCANON || MODE == M_INVSRC) ? 3 : 4;
 }
 template <int P, int MODE, int RED, int LR>
 __global__ __launch_bounds__(64 * kSplitWaves) __attribute__((amdgpu_waves_per_eu(split_waves<P, MODE, LR>())))
@@ -391,6 +399,9 @@ void k_mult_split(MultBatch B) {
     const bool site = active && w < 2;  // wavefronts 0 and 1 finish the sites
     const int Vh = a.g.Vh;
     constexpr bool CEN = MODE != M_HOPINV;
+    constexpr bool FULL = MODE == M_DFULL || MODE == M_DCANON;
+    // both parities of one launch read each link: through the cache
+    constexpr bool NT = MODE != M_DCANON;
     // the clover block b acts on up - dn (0) or up + dn (1)
     Herm6<R> M;
     R cs = R(1);
@@ -403,7 +414,7 @@ void k_mult_split(MultBatch B) {
             M = CloverIO<P>::template load<true>(a.clov, Vh, i, w);
         }
         // (both wavefronts read the whole centre here, through the cache)
-        if constexpr (MODE == M_DFULL || MODE == M_INVSRC) half_load<P, false>(a.center, i, 1 - w, oth);
+        if constexpr (FULL || MODE == M_INVSRC) half_load<P, false>(a.center, i, 1 - w, oth);
     }
     // wavefronts 2 and 3 hold a half of the fused dot's operand in its place
     if constexpr (CEN) {
@@ -417,10 +428,10 @@ void k_mult_split(MultBatch B) {
         if (active) {
             const SiteCoord c = eo_coords(a.g, i, a.out_par);
             switch (w) {
-            case 0: hop_dir<P, 0, true, LR>(a, c, i, acc); break;
-            case 1: hop_dir<P, 1, true, LR>(a, c, i, acc); break;
-            case 2: hop_dir<P, 2, true, LR>(a, c, i, acc); break;
-            default: hop_dir<P, 3, true, LR>(a, c, i, acc); break;
+            case 0: hop_dir<P, 0, NT, LR>(a, c, i, acc); break;
+            case 1: hop_dir<P, 1, NT, LR>(a, c, i, acc); break;
+            case 2: hop_dir<P, 2, NT, LR>(a, c, i, acc); break;
+            default: hop_dir<P, 3, NT, LR>(a, c, i, acc); break;
             }
         }
 #pragma unroll
@@ -428,7 +439,7 @@ void k_mult_split(MultBatch B) {
     }
     __syncthreads();
     const R coef = (R)a.coef;
-    cx<R> own[6];  // the hopping sum's own half (M_DFULL)
+    cx<R> own[6];  // the hopping sum's own half (FULL)
     if (site) {
         cx<R> v[6], y[6];
 #pragma unroll
@@ -438,7 +449,7 @@ void k_mult_split(MultBatch B) {
             for (int q = 0; q < 2; q++)
                 h[q] = (part[0][6 * q + k][lane] + part[1][6 * q + k][lane]) +
                        (part[2][6 * q + k][lane] + part[3][6 * q + k][lane]);
-            if (MODE == M_DFULL) {
+            if (FULL) {
                 own[k] = w ? h[1] : h[0];
                 h[0] = w ? oth[k] : cen[k];
                 h[1] = w ? cen[k] : oth[k];
@@ -461,7 +472,7 @@ void k_mult_split(MultBatch B) {
             cx<R> t = w ? yp - ym : yp + ym;
             if (P == P16) t = cs * t;
             if (MODE == M_DHAT) t = cen[k] + coef * t;
-            if (MODE == M_DFULL) t = t + coef * own[k];
+            if (FULL) t = t + coef * own[k];
             out[k] = t;
         }
     }
@@ -475,7 +486,23 @@ void k_mult_split(MultBatch B) {
         __syncthreads();
         if (site) m = fmaxf(m, mx[1 - w][lane]);
     }
-    if (site) half_store<P>(a.out, i, w, out, m);
+    if constexpr (MODE == M_DCANON) {
+        // through LDS, so that the canonical sites leave as whole 192-byte pieces
+        double2(*st)[13] = reinterpret_cast<double2(*)[13]>(part);  // 13: as kPadSpin in layout.hip
+        if (site) {
+#pragma unroll
+            for (int k = 0; k < 6; k++) st[lane][6 * w + k] = make_double2((double)out[k].re, (double)out[k].im);
+        }
+        __syncthreads();
+        const int live = min(64, Vh - lb * 64) * 12;
+        for (int e = threadIdx.x; e < live; e += 64 * kSplitWaves) {
+            const int q = e / 12;
+            const SiteCoord c = eo_coords(a.g, lb * 64 + q, a.out_par);
+            st_stream((double2 *)a.out + (size_t)(c.x + a.g.L[0] * c.row) * 12 + (e - 12 * q), st[q][e - 12 * q]);
+        }
+    } else {
+        if (site) half_store<P>(a.out, i, w, out, m);
+    }
     if constexpr (RED != R_NONE) {
         // wavefronts 0 and 1 sum what they hold, 2 and 3 the dot with the
         // operand they loaded
@@ -507,8 +534,8 @@ void k_mult_split(MultBatch B) {
 // (non-temporal) instance; the kernels use none of it
 template <int P, int MODE, int RED, int LR>
 void launch_nt(const MultBatch &B, int blocks, int bs, unsigned lds, hipStream_t s) {
-    if constexpr (MODE == M_HOPINV || MODE == M_DHAT || MODE == M_DFULL || MODE == M_INVSRC) {
-        if (bs == kSplitBlock) {
+    if constexpr (MODE != M_CLOV && (MODE != M_DFULL || P == P64)) {
+        if (MODE == M_DCANON || bs == kSplitBlock) {
             // the cap counts the kernel's own LDS
             constexpr unsigned own = sizeof(cx<typename Real<P>::T>) * 64 * (12 * kSplitWaves + 12);
             const unsigned dyn = lds > own ? lds - own : 0;
@@ -516,10 +543,12 @@ void launch_nt(const MultBatch &B, int blocks, int bs, unsigned lds, hipStream_t
             return;
         }
     }
-    if (B.h.interleave)
-        hipLaunchKernelGGL((k_mult<P, MODE, RED, false, LR>), dim3(blocks), dim3(bs), 0, s, B);
-    else
-        hipLaunchKernelGGL((k_mult<P, MODE, RED, true, LR>), dim3(blocks), dim3(bs), lds, s, B);
+    if constexpr (MODE != M_DCANON) {
+        if (B.h.interleave)
+            hipLaunchKernelGGL((k_mult<P, MODE, RED, false, LR>), dim3(blocks), dim3(bs), 0, s, B);
+        else
+            hipLaunchKernelGGL((k_mult<P, MODE, RED, true, LR>), dim3(blocks), dim3(bs), lds, s, B);
+    }
 }
 
 // reconstruct-8 and full-link instances exist for the FP32 stencil only
@@ -550,6 +579,9 @@ void dispatch_mode(const MultBatch &B, int mode, int red, int blocks, int bs, un
         } else launch_one<P, M_DHAT, R_NONE>(B, blocks, bs, lds, s, lr);
         break;
     case M_DFULL: launch_one<P, M_DFULL, R_NONE>(B, blocks, bs, lds, s, lr); break;
+    case M_DCANON:
+        if constexpr (P != P16) launch_one<P, M_DCANON, R_NONE>(B, blocks, bs, lds, s, lr);
+        break;
     case M_INVSRC: launch_one<P, M_INVSRC, R_NONE>(B, blocks, bs, lds, s, lr); break;
     case M_CLOV: launch_one<P, M_CLOV, R_NONE>(B, blocks, bs, lds, s, lr); break;
     }
@@ -563,6 +595,7 @@ double mult_spinor_bytes(int prec, int mode, int red, int Vh) {
     const double S = (double)spinor_site_bytes(prec) * Vh;
     double b = 2 * S;                                                    // input (once) + output
     if (mode == M_DHAT || mode == M_DFULL || mode == M_INVSRC) b += S;  // centre vector
+    if (mode == M_DCANON) b += (double)spinor_site_bytes(P64) * Vh;     // centre, and a complex128 output
     if (red != R_NONE) b += S;                                           // aux vector
     return b;
 }
@@ -570,7 +603,7 @@ double mult_operator_bytes(int prec, int mode, int lr, int Vh) {
     double b = 0;
     const int lb = lr == 8 ? 32 : lr == 18 ? 72 : link_site_bytes(prec);
     if (mode != M_CLOV) b += 8 * (double)lb * Vh;
-    b += (double)clover_site_bytes(prec) * Vh;
+    b += (mode == M_DCANON ? 2 : 1) * (double)clover_site_bytes(prec) * Vh;  // M_DCANON: both parities'
     return b;
 }
 
@@ -1461,9 +1494,10 @@ static StencilForm stencil_form(const MultCall *calls, int n) {
         same = calls[k].lat == c0.lat && calls[k].prec == c0.prec && calls[k].mode == c0.mode &&
                calls[k].red == c0.red && calls[k].out_par == c0.out_par && calls[k].coef == c0.coef;
     if (same) return F_MULTI;
+    if (c0.mode == M_DCANON) return F_SPLIT;
     // systems interleaved on one lattice share the operator through the cache,
     // which the split form's non-temporal loads would undo
-    bool split = c0.mode != M_CLOV;
+    bool split = c0.mode != M_CLOV && (c0.mode != M_DFULL || c0.prec == P64);  // (FP32: M_DCANON)
     for (int k = 0; split && k < n; k++)
         split = split_stencil(calls[k].lat, c0.prec) && (k == 0 || calls[k].lat != c0.lat);
     return split ? F_SPLIT : F_PLAIN;
@@ -1491,7 +1525,8 @@ int launch_mult_batch(hipStream_t s, const MultCall *calls, int n, wc_lattice *t
     for (int k = 0; k < n; k++) {
         const MultCall &c = calls[k];
         wc_lattice *lat = c.lat;
-        if (c.prec != c0.prec || c.mode != c0.mode || c.red != c0.red || c.out_par != c0.out_par)
+        if (c.prec != c0.prec || c.mode != c0.mode || c.red != c0.red ||
+            (c.out_par != c0.out_par && c.mode != M_DCANON))
             return wc_fail(WC_EINVAL, "batched stencil calls must share precision, mode, reduction and parity");
         if (c.bs != c0.bs) return wc_fail(WC_EINVAL, "batched stencil calls must share the block size");
         same = same && (lat == c0.lat);
