@@ -209,9 +209,25 @@ __device__ __forceinline__ void hop_dir(const MultKArgs &a, const SiteCoord &c, 
     }
 }
 
-// NT: links and clover read once per launch (one system) use non-temporal
-// loads; a launch that serves several systems on one lattice reads them
-// through the cache so that the blocks of the other systems hit in L2.
+// How a stencil launch reads the operator.  SHARED: links and clover through the
+// cache, since the launch serves several systems (or both parities) on one
+// lattice.  STREAM: each read once by its one system, non-temporal.  KEEP: the
+// clover streams, the links go through the cache: MULT and the D-hat half after
+// it read the same links, and where they fit in the last-level cache
+// the next launch finds them there.  The clover, read by every second launch
+// only, would push them out: cached as well, a solve at 24^2x32x48 took 429 us
+// per inner iteration instead of 387 (streamed links: 409).
+//
+// kKeepLinkBytes: up to which size of a launch's links, over all its lattices.
+// The cache holds 256 MB, and spinors and clover pass through it too.  us per
+// inner iteration, STREAM -> KEEP: FP32 16^4 (13 MB) 69.9 -> 65.2, 16^3x32 91.1
+// -> 85.3, 24^3x48 (127 MB) 322 -> 306, 24^2x32x48 (170 MB) 409 -> 387, but
+// 28^2x32x48 (231 MB) 539 -> 548 and 32^3x48 (302 MB) 687 -> 735; FP64
+// 12x14x10x18 67.8 -> 63.1, 20^3x40 (123 MB) 352 -> 332, 24^3x48 (255 MB) 679 ->
+// 697; FP16 24^3x48 (64 MB) 219 -> 214, 32^3x48 (151 MB) 417 -> 384.  The
+// multi-system kernel reads a link once for all its systems and gained nothing.
+constexpr double kKeepLinkBytes = 192e6;
+enum OperatorReads { SHARED = 0, KEEP = 1, STREAM = 2 };
 // The one-system FP16 MULT and D-hat instances are held to four waves per
 // SIMD (128 VGPRs; they use about 103 with both hops' loads in flight, hop_dir).
 // Five waves at 96 VGPRs helped the form with one hop's loads in flight
@@ -219,14 +235,15 @@ __device__ __forceinline__ void hop_dir(const MultKArgs &a, const SiteCoord &c, 
 // runs at 100.7 us; four waves with two hops' loads run at 83.9-84.7 us.
 // The reconstruct-8 FP32 instances, with both hops' loads in flight, are held
 // to four waves per SIMD in the same way (118-122 VGPRs).
-template <int P, int MODE, int RED, bool NT, int LR>
+template <int P, int MODE, int RED, int OPR, int LR>
 constexpr int stencil_waves() {
-    return ((P == P16 || (P == P32 && LR == 8)) && NT && (MODE == M_HOPINV || MODE == M_DHAT)) ? 4 : 1;
+    return ((P == P16 || (P == P32 && LR == 8)) && OPR != SHARED && (MODE == M_HOPINV || MODE == M_DHAT)) ? 4 : 1;
 }
-template <int P, int MODE, int RED, bool NT, int LR>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(stencil_waves<P, MODE, RED, NT, LR>())))
+template <int P, int MODE, int RED, int OPR, int LR>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(stencil_waves<P, MODE, RED, OPR, LR>())))
 void k_mult(MultBatch B) {
     using R = typename Real<P>::T;
+    constexpr bool NT = OPR != SHARED, LNT = OPR == STREAM;  // clover, links
     int s, lb;
     batch_locate(B.h, xcd_block(blockIdx.x, gridDim.x, B.h.chunk), s, lb);
     const MultKArgs &a = B.d[s];
@@ -244,10 +261,10 @@ void k_mult(MultBatch B) {
         for (int k = 0; k < 12; k++) acc.c[k] = {R(0), R(0)};
         if (MODE != M_CLOV) {
             const SiteCoord c = eo_coords(a.g, i, a.out_par);
-            hop_dir<P, 0, NT, LR>(a, c, i, acc);
-            hop_dir<P, 1, NT, LR>(a, c, i, acc);
-            hop_dir<P, 2, NT, LR>(a, c, i, acc);
-            hop_dir<P, 3, NT, LR>(a, c, i, acc);
+            hop_dir<P, 0, LNT, LR>(a, c, i, acc);
+            hop_dir<P, 1, LNT, LR>(a, c, i, acc);
+            hop_dir<P, 2, LNT, LR>(a, c, i, acc);
+            hop_dir<P, 3, LNT, LR>(a, c, i, acc);
         }
         const R coef = (R)a.coef;
         if (MODE == M_HOPINV) {
@@ -382,7 +399,7 @@ __device__ __forceinline__ void half_store(void *base, int i, int h, const cx<ty
 template <int P, int MODE, int LR> constexpr int split_waves() {
     return P == P64 ? 2 : (LR == 8 || MODE == M_DFULL || MODE == M_DCANON || MODE == M_INVSRC) ? 3 : 4;
 }
-template <int P, int MODE, int RED, int LR>
+template <int P, int MODE, int RED, int OPR, int LR>
 __global__ __launch_bounds__(64 * kSplitWaves) __attribute__((amdgpu_waves_per_eu(split_waves<P, MODE, LR>())))
 void k_mult_split(MultBatch B) {
     using R = typename Real<P>::T;
@@ -400,8 +417,7 @@ void k_mult_split(MultBatch B) {
     const int Vh = a.g.Vh;
     constexpr bool CEN = MODE != M_HOPINV;
     constexpr bool FULL = MODE == M_DFULL || MODE == M_DCANON;
-    // both parities of one launch read each link: through the cache
-    constexpr bool NT = MODE != M_DCANON;
+    constexpr bool LNT = OPR == STREAM;
     // the clover block b acts on up - dn (0) or up + dn (1)
     Herm6<R> M;
     R cs = R(1);
@@ -428,10 +444,10 @@ void k_mult_split(MultBatch B) {
         if (active) {
             const SiteCoord c = eo_coords(a.g, i, a.out_par);
             switch (w) {
-            case 0: hop_dir<P, 0, NT, LR>(a, c, i, acc); break;
-            case 1: hop_dir<P, 1, NT, LR>(a, c, i, acc); break;
-            case 2: hop_dir<P, 2, NT, LR>(a, c, i, acc); break;
-            default: hop_dir<P, 3, NT, LR>(a, c, i, acc); break;
+            case 0: hop_dir<P, 0, LNT, LR>(a, c, i, acc); break;
+            case 1: hop_dir<P, 1, LNT, LR>(a, c, i, acc); break;
+            case 2: hop_dir<P, 2, LNT, LR>(a, c, i, acc); break;
+            default: hop_dir<P, 3, LNT, LR>(a, c, i, acc); break;
             }
         }
 #pragma unroll
@@ -531,59 +547,64 @@ void k_mult_split(MultBatch B) {
 }
 
 // lds: dynamic LDS bytes that cap the workgroups per CU of the one-system
-// (non-temporal) instance; the kernels use none of it
-template <int P, int MODE, int RED, int LR>
-void launch_nt(const MultBatch &B, int blocks, int bs, unsigned lds, hipStream_t s) {
-    if constexpr (MODE != M_CLOV && (MODE != M_DFULL || P == P64)) {
+// instances; the kernels use none of it
+template <int P, int MODE, int RED, int OPR, int LR>
+void launch_as(const MultBatch &B, int blocks, int bs, unsigned lds, hipStream_t s) {
+    if constexpr (MODE == M_DCANON || (OPR != SHARED && MODE != M_CLOV && (MODE != M_DFULL || P == P64))) {
         if (MODE == M_DCANON || bs == kSplitBlock) {
             // the cap counts the kernel's own LDS
             constexpr unsigned own = sizeof(cx<typename Real<P>::T>) * 64 * (12 * kSplitWaves + 12);
             const unsigned dyn = lds > own ? lds - own : 0;
-            hipLaunchKernelGGL((k_mult_split<P, MODE, RED, LR>), dim3(blocks), dim3(64 * kSplitWaves), dyn, s, B);
+            hipLaunchKernelGGL((k_mult_split<P, MODE, RED, OPR, LR>), dim3(blocks), dim3(64 * kSplitWaves), dyn, s, B);
             return;
         }
     }
-    if constexpr (MODE != M_DCANON) {
-        if (B.h.interleave)
-            hipLaunchKernelGGL((k_mult<P, MODE, RED, false, LR>), dim3(blocks), dim3(bs), 0, s, B);
-        else
-            hipLaunchKernelGGL((k_mult<P, MODE, RED, true, LR>), dim3(blocks), dim3(bs), lds, s, B);
+    if constexpr (MODE != M_DCANON)
+        hipLaunchKernelGGL((k_mult<P, MODE, RED, OPR, LR>), dim3(blocks), dim3(bs), lds, s, B);
+}
+
+template <int P, int MODE, int RED, int LR>
+void launch_nt(const MultBatch &B, int blocks, int bs, unsigned lds, hipStream_t s, bool keep) {
+    if (MODE == M_DCANON || B.h.interleave) return launch_as<P, MODE, RED, SHARED, LR>(B, blocks, bs, lds, s);
+    if constexpr (MODE == M_HOPINV || MODE == M_DHAT) {
+        if (keep) return launch_as<P, MODE, RED, KEEP, LR>(B, blocks, bs, lds, s);
     }
+    if constexpr (MODE != M_DCANON) launch_as<P, MODE, RED, STREAM, LR>(B, blocks, bs, lds, s);
 }
 
 // reconstruct-8 and full-link instances exist for the FP32 stencil only
 template <int P, int MODE, int RED>
-void launch_one(const MultBatch &B, int blocks, int bs, unsigned lds, hipStream_t s, int lr) {
+void launch_one(const MultBatch &B, int blocks, int bs, unsigned lds, hipStream_t s, int lr, bool keep) {
     if constexpr (P == P32) {
         if (lr == 8) {
-            launch_nt<P, MODE, RED, 8>(B, blocks, bs, lds, s);
+            launch_nt<P, MODE, RED, 8>(B, blocks, bs, lds, s, keep);
             return;
         }
         if (lr == 18) {
-            launch_nt<P, MODE, RED, 18>(B, blocks, bs, lds, s);
+            launch_nt<P, MODE, RED, 18>(B, blocks, bs, lds, s, keep);
             return;
         }
     }
-    launch_nt<P, MODE, RED, 12>(B, blocks, bs, lds, s);
+    launch_nt<P, MODE, RED, 12>(B, blocks, bs, lds, s, keep);
 }
 
 template <int P>
-void dispatch_mode(const MultBatch &B, int mode, int red, int blocks, int bs, unsigned lds, hipStream_t s, int lr) {
+void dispatch_mode(const MultBatch &B, int mode, int red, int blocks, int bs, unsigned lds, hipStream_t s, int lr, bool keep) {
     switch (mode) {
-    case M_HOPINV: launch_one<P, M_HOPINV, R_NONE>(B, blocks, bs, lds, s, lr); break;
+    case M_HOPINV: launch_one<P, M_HOPINV, R_NONE>(B, blocks, bs, lds, s, lr, keep); break;
     case M_DHAT:
-        if (red == R_DOT) launch_one<P, M_DHAT, R_DOT>(B, blocks, bs, lds, s, lr);
-        else if (red == R_STEP) launch_one<P, M_DHAT, R_STEP>(B, blocks, bs, lds, s, lr);
+        if (red == R_DOT) launch_one<P, M_DHAT, R_DOT>(B, blocks, bs, lds, s, lr, keep);
+        else if (red == R_STEP) launch_one<P, M_DHAT, R_STEP>(B, blocks, bs, lds, s, lr, keep);
         else if (red == R_DOTNORM) {
-            if constexpr (P == P64) launch_one<P, M_DHAT, R_DOTNORM>(B, blocks, bs, lds, s, lr);  // outer loop only
-        } else launch_one<P, M_DHAT, R_NONE>(B, blocks, bs, lds, s, lr);
+            if constexpr (P == P64) launch_one<P, M_DHAT, R_DOTNORM>(B, blocks, bs, lds, s, lr, keep);  // outer loop only
+        } else launch_one<P, M_DHAT, R_NONE>(B, blocks, bs, lds, s, lr, keep);
         break;
-    case M_DFULL: launch_one<P, M_DFULL, R_NONE>(B, blocks, bs, lds, s, lr); break;
+    case M_DFULL: launch_one<P, M_DFULL, R_NONE>(B, blocks, bs, lds, s, lr, keep); break;
     case M_DCANON:
-        if constexpr (P != P16) launch_one<P, M_DCANON, R_NONE>(B, blocks, bs, lds, s, lr);
+        if constexpr (P != P16) launch_one<P, M_DCANON, R_NONE>(B, blocks, bs, lds, s, lr, keep);
         break;
-    case M_INVSRC: launch_one<P, M_INVSRC, R_NONE>(B, blocks, bs, lds, s, lr); break;
-    case M_CLOV: launch_one<P, M_CLOV, R_NONE>(B, blocks, bs, lds, s, lr); break;
+    case M_INVSRC: launch_one<P, M_INVSRC, R_NONE>(B, blocks, bs, lds, s, lr, keep); break;
+    case M_CLOV: launch_one<P, M_CLOV, R_NONE>(B, blocks, bs, lds, s, lr, keep); break;
     }
 }
 
@@ -599,10 +620,10 @@ double mult_spinor_bytes(int prec, int mode, int red, int Vh) {
     if (red != R_NONE) b += S;                                           // aux vector
     return b;
 }
+int link_bytes_per_site(int prec, int lr) { return lr == 8 ? 32 : lr == 18 ? 72 : link_site_bytes(prec); }
 double mult_operator_bytes(int prec, int mode, int lr, int Vh) {
     double b = 0;
-    const int lb = lr == 8 ? 32 : lr == 18 ? 72 : link_site_bytes(prec);
-    if (mode != M_CLOV) b += 8 * (double)lb * Vh;
+    if (mode != M_CLOV) b += 8 * (double)link_bytes_per_site(prec, lr) * Vh;
     b += (mode == M_DCANON ? 2 : 1) * (double)clover_site_bytes(prec) * Vh;  // M_DCANON: both parities'
     return b;
 }
@@ -1520,7 +1541,7 @@ int launch_mult_batch(hipStream_t s, const MultCall *calls, int n, wc_lattice *t
     B.h.S = n;
     B.h.off[0] = 0;
     bool same = true;
-    double bytes = 0;
+    double bytes = 0, link_bytes = 0;
     const int lr = c0.prec == P32 ? c0.lat->recon : 12;  // link form of the FP32 stencil
     for (int k = 0; k < n; k++) {
         const MultCall &c = calls[k];
@@ -1553,7 +1574,10 @@ int launch_mult_batch(hipStream_t s, const MultCall *calls, int n, wc_lattice *t
         bytes += mult_spinor_bytes(c.prec, c.mode, c.red, lat->Vh);
         bool seen = false;
         for (int j = 0; j < k; j++) seen = seen || (calls[j].lat == lat);
-        if (!seen) bytes += mult_operator_bytes(c.prec, c.mode, lr, lat->Vh);
+        if (!seen) {
+            bytes += mult_operator_bytes(c.prec, c.mode, lr, lat->Vh);
+            link_bytes += 8 * (double)link_bytes_per_site(c.prec, lr) * lat->Vh;
+        }
         if (c.mode != M_CLOV) lat->dslash_count++;
     }
     B.h.interleave = (same && n > 1) ? 1 : 0;
@@ -1588,9 +1612,10 @@ int launch_mult_batch(hipStream_t s, const MultCall *calls, int n, wc_lattice *t
     }
     const unsigned lds = B.h.interleave ? 0u : cap_lds_bytes(c0.lat, c0.prec, split ? 64 * kSplitWaves : bs, c0.mode);
     const int shape = split ? kSplitBlock : bs;
-    if (c0.prec == P64) dispatch_mode<P64>(B, c0.mode, c0.red, blocks, shape, lds, s, 12);
-    else if (c0.prec == P32) dispatch_mode<P32>(B, c0.mode, c0.red, blocks, shape, lds, s, lr);
-    else dispatch_mode<P16>(B, c0.mode, c0.red, blocks, shape, lds, s, 12);
+    const bool keep = link_bytes <= kKeepLinkBytes;
+    if (c0.prec == P64) dispatch_mode<P64>(B, c0.mode, c0.red, blocks, shape, lds, s, 12, keep);
+    else if (c0.prec == P32) dispatch_mode<P32>(B, c0.mode, c0.red, blocks, shape, lds, s, lr, keep);
+    else dispatch_mode<P16>(B, c0.mode, c0.red, blocks, shape, lds, s, 12, keep);
     WC_HIP(hipGetLastError());
     if (tl->timing) timing_end(tl, t);
     if (c0.red != R_NONE && c0.mode == M_DHAT && c0.red_to.result) {
