@@ -1,7 +1,9 @@
 // The hopping stencil with spin projection and its clover epilogues (MULT of
 // Sec. II-B, eq. 9, and the Schur operator D-hat_ee of eq. 8).
 //
-// One thread per output site of one parity.  For each of the 8 directions the
+// k_mult takes one thread per output site of one parity, k_mult_split four (a
+// wavefront per direction of a 64-site tile), and k_mult_multi one tile for all
+// systems of a batch.  For each of the 8 directions the
 // neighbour spinor (opposite parity) is projected to a two-spin half spinor,
 // multiplied by U_mu(n) (forward) or U_mu(n - mu)^dagger (backward), and
 // expanded back into the accumulator (eq. 4).  In the Dirac representation:
@@ -10,12 +12,13 @@
 //   (1 - g_t) psi = (0, 2 psi_d),    (1 + g_t) psi = (2 psi_u, 0)
 // so each direction costs two 3x3 complex matrix-vector products.
 // Neighbour spinors are ordinary cached loads (each is read by 8 output sites);
-// links and clover blocks are read exactly once per launch and use
-// non-temporal loads so they do not evict the spinor working set.
+// clover blocks, and links too large for the last-level cache, are read exactly
+// once per launch and use non-temporal loads so they do not evict the spinor
+// working set (OperatorReads below).
 //
 // Workgroups are handed to the 8 XCDs round-robin, and each XCD has its own
-// L2.  The block index is remapped so that XCD k sweeps one contiguous slab of
-// the lattice: the y, z and t neighbours a block needs were then loaded by
+// L2.  The block index is remapped (xcd_block) so that XCD k sweeps contiguous
+// chunks of the lattice: the y and z neighbours a block needs were then loaded by
 // blocks of the same XCD shortly before, and hit in that XCD's L2.
 #include <hip/hip_cooperative_groups.h>
 
@@ -1112,9 +1115,8 @@ template <int P> void dispatch_mrhs(const MrhsArgs &A, int mode, int red, hipStr
 // The whole inner loop (Algorithm 2) in one cooperative launch, for lattices
 // small enough that every workgroup is resident at once.  Each phase of an
 // iteration ends in a grid-wide barrier instead of a kernel boundary; every
-// block then sums the reduction partials itself, in the same order as the
-// finalize kernel of the launched path, so all blocks take the same
-// decisions and leave the loop together.  The per-site arithmetic is that of
+// block then sums the reduction partials itself, all in one order, so all
+// blocks take the same decisions and leave the loop together.  The per-site arithmetic is that of
 // the stencil and vector kernels, and the scalars and flags are left exactly
 // as the launched path leaves them, so the host finishes the call the same
 // way.  Partials alternate between two buffers: a buffer is written again

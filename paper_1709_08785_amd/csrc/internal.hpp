@@ -235,8 +235,9 @@ struct wc_lattice {
 };
 
 // systems per thread of the multi-system stencil in precision prec: the
-// setting, else 2 for FP32 and 4 for FP16 (the faster of the two in each
-// precision on the 12-source batch)
+// setting, else 2 for FP32 and 4 for FP16.  Where a launch takes the systems one
+// after the other (k_mult_multi) any value but 0 means just that; in FP16's
+// other form 4 is the faster on the 12-source batch
 inline int mrhs_for(const wc_lattice *lat, int prec) {
     if (lat->mrhs >= 0) return lat->mrhs;
     return prec == P16 ? 4 : 2;
@@ -395,8 +396,8 @@ inline unsigned cap_lds_bytes(const wc_lattice *lat, int prec, int bs, int mode 
 // thread per site.  FP64 and the FP32 two-column and full links always do: it
 // is faster at every size measured (8^4 to 48^3x96).  FP16 storage and
 // reconstruct-8 links spend more of their time in arithmetic, and while two
-// wavefronts finish a tile the other two have none: they take it up to four tiles per compute
-// unit, where latency decides (D-hat_ee in FP16: 16^4 18.5 -> 14.6 us, 16^3x32
+// wavefronts finish a tile the other two have none: they take it up to four tiles per
+// compute unit, where latency decides (D-hat_ee in FP16: 16^4 18.5 -> 14.6 us, 16^3x32
 // 22.1 -> 21.2, but 16^2x24x32 29.2 -> 31.2 and 32^3x64 170 -> 207;
 // reconstruct-8: 16^3x32 33.3 -> 30.9, 24^3x48 106 -> 110).
 constexpr int kSplitTiles = 1024;

@@ -2,9 +2,10 @@
 //
 // Stage 1 (inside the producing kernel): each block folds its per-thread
 // values over its wavefronts and an LDS pass in a fixed order and writes
-// one partial per value with a plain store.  Stage 2 is a separate one-block
-// kernel (k_finalize, blas.hip) that sums the partials in block order and runs
-// the scalar logic of the solver.  The kernel boundary makes the partials
+// one partial per value with a plain store.  Stage 2 sums the partials in a
+// fixed order and runs the scalar logic of the solver: in the inner loop in every
+// block of the kernel that consumes them (sum_partials), elsewhere in a separate
+// one-block kernel (k_finalize, blas.hip).  The kernel boundary makes the partials
 // visible; no block ever waits on, or fences against, another block, so the
 // per-XCD L2 caches keep the stencil's working set.  Accumulation is FP64 and
 // the summation order is fixed, so results are bit-reproducible.
