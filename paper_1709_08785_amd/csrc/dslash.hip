@@ -226,7 +226,7 @@ __device__ __forceinline__ void hop_dir(const MultKArgs &a, const SiteCoord &c, 
 // inner iteration, STREAM -> KEEP: FP32 16^4 (13 MB) 69.9 -> 65.2, 16^3x32 91.1
 // -> 85.3, 24^3x48 (127 MB) 322 -> 306, 24^2x32x48 (170 MB) 409 -> 387, but
 // 28^2x32x48 (231 MB) 539 -> 548 and 32^3x48 (302 MB) 687 -> 735; FP64
-// 12x14x10x18 67.8 -> 63.1, 20^3x40 (123 MB) 352 -> 332, 24^3x48 (255 MB) 679 ->
+// 12x14x10x18 67.8 -> 63.1, 20^3x40 (184 MB) 352 -> 332, 24^3x48 (382 MB) 679 ->
 // 697; FP16 24^3x48 (64 MB) 219 -> 214, 32^3x48 (151 MB) 417 -> 384.  The
 // multi-system kernel reads a link once for all its systems and gained nothing.
 constexpr double kKeepLinkBytes = 192e6;

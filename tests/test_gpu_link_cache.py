@@ -24,7 +24,7 @@ KAPPA = 0.13
 BASE = (14, 4, 4, 48)
 
 
-# MB of links: FP64 101 | 202, FP32 101 | 202 (two columns), 151 | 303 (full), FP16 101
+# MB of links: FP64 155 | 310, FP32 103 | 202 (two columns), 152 | 303 (full), 135 (8 reals), FP16 101
 @pytest.mark.parametrize("prec,recon,reps", [
     (wc.FP64, 12, (1, 5, 5)), (wc.FP64, 12, (2, 5, 5)),
     (wc.FP32, 12, (2, 5, 5)), (wc.FP32, 12, (2, 7, 7)),
