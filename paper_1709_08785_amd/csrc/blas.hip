@@ -20,8 +20,7 @@
 // A reduction is not finished by a kernel of its own: the update that consumes
 // it sums the partials in every block (in one order, so all blocks take the same
 // decisions), and block 0 records scalars and flags.  No kernel reads a word
-// that it also writes, except the done flag, which is only raised where every
-// block leaves without touching the vectors.  From kFoldPartials partials on,
+// that another block of it may be writing (FlagSlot for the done code).  From kFoldPartials partials on,
 // re-reading them in every block would cost more than it saves, and a fold
 // kernel first sums them once.  The convergence test of ||r||^2 is taken by the
 // next V_INNER_A, or by FIN_CHECK before a host read; that of ||s||^2 by
@@ -81,7 +80,12 @@ template <int OP, int P, int XP> __global__ __launch_bounds__(kBlock) void k_vec
     int s, lb;
     batch_locate(B.h, blockIdx.x, s, lb);
     const VecCall &c = B.c[s];
-    if (c.guard && c.fl[F_DONE]) return;
+    // the guard word, and the one that a stop goes to
+    constexpr int kIn = OP == V_INNER_B ? F_DONE_A : F_DONE, kOut = OP == V_INNER_A ? F_DONE_A : F_DONE;
+    if (c.guard && c.fl[kIn]) {
+        if ((OP == V_INNER_A || OP == V_INNER_B) && lb == 0 && threadIdx.x == 0) c.fl[kOut] = c.fl[kIn];
+        return;
+    }
     const int Vh = c.Vh;
     const int i = lb * (int)blockDim.x + threadIdx.x;  // 64, 128 or 256 sites per block
     const bool active = i < Vh;
@@ -175,7 +179,7 @@ template <int OP, int P, int XP> __global__ __launch_bounds__(kBlock) void k_vec
         if (stop != DONE_NO || !finite_c(al)) {
             if (first) {
                 c.fl[F_STOPPH] = stop != DONE_NO ? 2 : 1;
-                c.fl[F_DONE] = stop != DONE_NO ? stop : DONE_BREAK;
+                c.fl[kOut] = stop != DONE_NO ? stop : DONE_BREAK;
             }
             return;
         }
@@ -219,7 +223,7 @@ template <int OP, int P, int XP> __global__ __launch_bounds__(kBlock) void k_vec
             if (first) {
                 if (!half) c.fl[F_ITERS] += 1;
                 c.fl[F_STOPPH] = half ? 1 : 2;
-                c.fl[F_DONE] = half && isfinite(ss) ? DONE_HALF : DONE_BREAK;
+                c.fl[kOut] = half && isfinite(ss) ? DONE_HALF : DONE_BREAK;
             }
             return;
         }
@@ -487,6 +491,7 @@ template <int N> __global__ __launch_bounds__(kBlock) void k_finalize(FinBatch B
         sc[S_RHO0 + 1] = 0.0;
         sc[S_TOL2] = f.tol2;
         fl[F_DONE] = DONE_NO;
+        fl[F_DONE_A] = DONE_NO;
         fl[F_ITERS] = 0;
         fl[F_STOPPH] = 0;
         break;

@@ -157,7 +157,7 @@ void timing_end(wc_lattice *lat, TimedLaunch &t) {
 void timing_settle(wc_lattice *lat, size_t from, const std::vector<StopPoint> &stops) {
     auto stopped = [&](const int *fl, int iter, int phase) {
         for (const auto &sp : stops)
-            if (sp.fl == fl) return iter > sp.iter || (iter == sp.iter && phase >= sp.phase);
+            if (sp.fl == fl || sp.fl + F_DONE_A == fl) return iter > sp.iter || (iter == sp.iter && phase >= sp.phase);
         return false;
     };
     for (size_t k = from; k < lat->launches.size(); k++) {

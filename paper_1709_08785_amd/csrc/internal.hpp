@@ -41,7 +41,14 @@ enum ScalarSlot {
 // F_STOPPH: where the inner loop stopped: 1 at the half-step check (after the
 // first D-hat), 2 at the full-step check (after the second), 3 when a grid
 // barrier of the one-launch loop ran out of time (the call then fails)
-enum FlagSlot { F_DONE = 0, F_ITERS = 1, F_STOPPH = 2, F_COUNT = 4 };
+// F_DONE and F_DONE_A: the done code.  The launched inner loop's two updates
+// raise it themselves, and other blocks of the same launch are then still to
+// read their guard.  So each update leaves the code in a word that its own
+// launch does not read, and passes on the one it does: V_INNER_A reads F_DONE
+// and writes F_DONE_A, V_INNER_B reads F_DONE_A and writes F_DONE, and a kernel
+// between them reads what the update before it wrote.  All other loops, and the
+// host, use F_DONE alone.
+enum FlagSlot { F_DONE = 0, F_ITERS = 1, F_STOPPH = 2, F_DONE_A = 3, F_COUNT = 4 };
 enum DoneCode { DONE_NO = 0, DONE_FULL = 1, DONE_HALF = 2, DONE_BREAK = 4 };
 
 enum { NUM_LEVELS = 2 };  // 0 = inner loop, 1 = outer / FP64 loop
@@ -490,7 +497,7 @@ struct VecCall {
     double tol2;
     double coef;
     int iter;          // iteration index (outer loop)
-    int guard;         // skip when fl[F_DONE] != 0
+    int guard;         // skip when the done code is set (FlagSlot)
     int bs;            // threads per block of the launch (64, 128 or 256; 0 = 256)
 };
 // prec: storage precision of the inner vectors (the inner solution x is FP64

@@ -198,7 +198,7 @@ constexpr int kFoldPartials = 1280;
 // the sources that the update after a reduction sums: the stencil's na values
 // (`stencil`) and the previous update's nb (`vec`), folded into the
 // scalar block first where some system has too many partials
-int inner_sources(Run &R, const std::vector<int> &act, int stencil, int na, int vec, int nb, const int *ns,
+int inner_sources(Run &R, const std::vector<int> &act, int stencil, int na, int vec, int nb, int guard, const int *ns,
                   SumSource *in0, SumSource *in1) {
     bool fold = false;
     FoldArgs f[kMaxSys];
@@ -213,7 +213,7 @@ int inner_sources(Run &R, const std::vector<int> &act, int stencil, int na, int 
     n = 0;
     for (int k : act) {
         double *out = S_(R, k).st->sc(0) + S_FOLD;
-        f[n] = FoldArgs{in0[n], in1[n], out, S_(R, k).st->fl(0) + F_DONE};
+        f[n] = FoldArgs{in0[n], in1[n], out, S_(R, k).st->fl(0) + guard};
         in0[n] = SumSource{out, 1};
         in1[n] = SumSource{out + na, 1};
         n++;
@@ -222,12 +222,12 @@ int inner_sources(Run &R, const std::vector<int> &act, int stencil, int na, int 
 }
 
 // D-hat of the inner loop with its sums (with r~ among them) left as partials,
-// ns[] of them per value
-int inner_dhat(Run &R, const std::vector<int> &act, int out_id, int in_id, int red, int slot, int *ns) {
+// ns[] of them per value; guard: the flag word that the update before it wrote
+int inner_dhat(Run &R, const std::vector<int> &act, int out_id, int in_id, int red, int slot, int guard, int *ns) {
     const int L = 0, P = R.iprec;
     if (int rc = mult_over(R, act, [&](int k) {
             MultCall c = mc(R, k, P, M_HOPINV, 1, W(R, k, W_ITMP), W(R, k, in_id), nullptr, 0.0);
-            c.done = S_(R, k).st->fl(L);
+            c.done = S_(R, k).st->fl(L) + guard;
             return c;
         }))
         return rc;
@@ -240,7 +240,7 @@ int inner_dhat(Run &R, const std::vector<int> &act, int out_id, int in_id, int r
         c.red = red;
         c.aux = W(R, k, W_IRT);
         c.red_to = RedTarget{partials(R, k, slot), nullptr};
-        c.done = s.st->fl(L);
+        c.done = s.st->fl(L) + guard;
         calls[n++] = c;
         R.dslash[k]++;
     }
@@ -271,15 +271,15 @@ int inner_chunk(Run &R, const std::vector<int> &act, int n, int base = 0) {
     };
     for (int j = 0; j < n; j++) {
         tag(base + j, 0);
-        if (int rc = inner_dhat(R, act, W_IQ, W_IP, R_DOT, PS_RQ, ns)) return rc;
-        if (int rc = inner_sources(R, act, PS_RQ, 2, PS_RR, 1, ns, in0, in1)) return rc;
+        if (int rc = inner_dhat(R, act, W_IQ, W_IP, R_DOT, PS_RQ, F_DONE, ns)) return rc;
+        if (int rc = inner_sources(R, act, PS_RQ, 2, PS_RR, 1, F_DONE, ns, in0, in1)) return rc;
         int i = 0;
         if (int rc = vec_over(R, act, V_INNER_A, P,
                               [&](int k) { return update(i++, PS_SS, vc(R, k, L, W(R, k, W_IR), W(R, k, W_IQ), W(R, k, W_IRT))); }))
             return rc;
         tag(base + j, 1);
-        if (int rc = inner_dhat(R, act, W_IT, W_IR, R_STEP, PS_STEP, ns)) return rc;
-        if (int rc = inner_sources(R, act, PS_STEP, 5, PS_SS, 3, ns, in0, in1)) return rc;
+        if (int rc = inner_dhat(R, act, W_IT, W_IR, R_STEP, PS_STEP, F_DONE_A, ns)) return rc;
+        if (int rc = inner_sources(R, act, PS_STEP, 5, PS_SS, 3, F_DONE_A, ns, in0, in1)) return rc;
         i = 0;
         if (int rc = vec_over(R, act, V_INNER_B, P, [&](int k) {
                 return update(i++, PS_RR, vc(R, k, L, W(R, k, W_IX), W(R, k, W_IR), W(R, k, W_IP), W(R, k, W_IT),
