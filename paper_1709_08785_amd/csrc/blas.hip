@@ -12,7 +12,9 @@
 // s = r - alpha q, V_INNER_B the rest: x, r and p.  p needs rho1 = <r~, r> of the
 // r being formed, which is <r~, s> - omega <r~, t>: the first is summed with the
 // half step, the second with the second D-hat, so x, r and p take one pass over
-// s, t, p, q instead of two.  (<r~, s> is zero in exact arithmetic, but its
+// s, t, p, q instead of two.  Both sums are over s and t as they are stored,
+// since r is formed from those: in FP16 storage, sums of the values before storage
+// double the error of rho.  (<r~, s> is zero in exact arithmetic, but its
 // rounding errors are of the size of the first residuals and stay in r: left
 // out, rho drowns in them, and an FP32 solve at 8^3x16 and kappa 0.1355 no
 // longer converged.)
@@ -195,10 +197,10 @@ template <int OP, int P, int XP> __global__ __launch_bounds__(kBlock) void k_vec
             for (int k = 0; k < 12; k++) rv.c[k] = rv.c[k] - alpha * qv.c[k];
             SpinorIO<P>::template store<kVNT>(c.a, Vh, i, rv);
 #pragma unroll
-            for (int k = 0; k < 12; k++) {
-                a[0] += norm2(rv.c[k]);
-                dot_acc(a[1 % NA], a[2 % NA], rtv.c[k], rv.c[k]);
-            }
+            for (int k = 0; k < 12; k++) a[0] += norm2(rv.c[k]);
+            as_stored<P>(rv);
+#pragma unroll
+            for (int k = 0; k < 12; k++) dot_acc(a[1 % NA], a[2 % NA], rtv.c[k], rv.c[k]);
         }
     } else if (OP == V_INNER_B) {
         // the half-step test, then omega = <t, s> / ||t||^2,
@@ -249,6 +251,7 @@ template <int OP, int P, int XP> __global__ __launch_bounds__(kBlock) void k_vec
                 a[0] += norm2(sv.c[k]);
             }
             SpinorIO<P>::template store<kVNT>(c.b, Vh, i, sv);
+            as_stored<P>(sv);
             const Spinor<R> qv = SpinorIO<P>::template load<kVNT>(c.e, Vh, i);
 #pragma unroll
             for (int k = 0; k < 12; k++) pv.c[k] = sv.c[k] + beta * (pv.c[k] - omega * qv.c[k]);

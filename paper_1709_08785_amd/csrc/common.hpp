@@ -303,6 +303,12 @@ template <> struct SpinorIO<P32> {
     }
 };
 
+// v as FP16 storage at site scale m gives it back (inv = 1 / m, 0 for a zero site)
+__device__ __forceinline__ cx<float> stored16(cx<float> v, float m, float inv) {
+    const float2 h = h2f(f2h(v.re * inv, v.im * inv));
+    return {m * h.x, m * h.y};
+}
+
 // FP16 storage: planes of uint4 (3 * 16 B) followed by a float scale plane at 48
 template <> struct SpinorIO<P16> {
     using R = float;
@@ -364,7 +370,20 @@ template <> struct SpinorIO<P16> {
         }
         st_op<NT>(tp<float, 52>(base, i, 48), m);
     }
+    // v as store() leaves it
+    __device__ static void stored(Spinor<R> &v) {
+        float m = 0.f;
+#pragma unroll
+        for (int k = 0; k < 12; k++) m = fmaxf(m, fmaxf(fabsf(v.c[k].re), fabsf(v.c[k].im)));
+        const float inv = m > 0.f ? 1.0f / m : 0.f;
+#pragma unroll
+        for (int k = 0; k < 12; k++) v.c[k] = stored16(v.c[k], m, inv);
+    }
 };
+// the values that memory keeps of v: FP16 storage rounds them
+template <int P, class R> __device__ __forceinline__ void as_stored(Spinor<R> &v) {
+    if constexpr (P == P16) SpinorIO<P16>::stored(v);
+}
 
 // ---------------------------------------------------------------------------
 // links: full 3x3 matrices in registers

@@ -303,6 +303,7 @@ void k_mult(MultBatch B) {
         if (active) {
             if (RED == R_STEP) {
                 red_add<true, true, 12>(v, ax.c, out.c);
+                as_stored<P>(out);
                 red_add<true, false, 12>(v + 3, SpinorIO<P>::template load<true>(a.aux, Vh, i).c, out.c);
             } else {
                 red_add<true, RED == R_DOTNORM, 12>(v, SpinorIO<P>::template load<true>(a.aux, Vh, i).c, out.c);
@@ -535,7 +536,10 @@ void k_mult_split(MultBatch B) {
         for (int k = 0; k < 6; k++) keep(cen[k]);
         if (site) {
 #pragma unroll
-            for (int k = 0; k < 6; k++) part[w][k][lane] = out[k];
+            for (int k = 0; k < 6; k++) {
+                if constexpr (P == P16 && RED == R_STEP) part[w][k][lane] = stored16(out[k], m, m > 0.f ? 1.0f / m : 0.f);
+                else part[w][k][lane] = out[k];
+            }
             red_add<RED == R_STEP, RED != R_DOT, 6>(v, cen, out);
         }
         __syncthreads();
@@ -810,6 +814,7 @@ __global__ __launch_bounds__(64 * kMrhsMaxGroups) void k_mult_mrhs(MrhsArgs A) {
                 if (RED == R_DOT) red_add<true, false, 12>(red[j], ax.c, acc[j].c);
                 if (RED == R_STEP) {
                     red_add<true, true, 12>(red[j], cen.c, acc[j].c);
+                    as_stored<P>(acc[j]);
                     red_add<true, false, 12>(red[j] + 3, ax.c, acc[j].c);
                 }
             } else {
@@ -1049,6 +1054,10 @@ __global__ __launch_bounds__(64 * kMultiWaves) __attribute__((amdgpu_waves_per_e
                 }
                 if (RED == R_STEP) {
                     red_add<true, true, 6>(r, cen, out);
+                    if constexpr (P == P16) {
+#pragma unroll
+                        for (int k = 0; k < 6; k++) out[k] = stored16(out[k], m, m > 0.f ? 1.0f / m : 0.f);
+                    }
                     red_add<true, false, 6>(r + 3, ax, out);
                 } else {
                     red_add<true, false, 6>(r, ax, out);

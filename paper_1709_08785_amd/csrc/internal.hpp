@@ -364,7 +364,8 @@ int launch_fold_batch(hipStream_t s, const FoldArgs *f, int n, int na, int nb);
 // M_DCANON: M_DFULL with the output in the canonical complex128 layout; one launch
 // takes both parities (split stencil only)
 enum MultMode { M_HOPINV = 0, M_DHAT = 1, M_DFULL = 2, M_INVSRC = 3, M_CLOV = 4, M_DCANON = 5 };
-// R_DOT <aux, out>; R_DOTNORM and ||out||^2; R_STEP <center, out>, ||out||^2, <aux, out>
+// R_DOT <aux, out>; R_DOTNORM and ||out||^2; R_STEP <center, out>, ||out||^2 and
+// <aux, out>, the last over out as it is stored (rho is made of it, and r of the stored out)
 enum MultRed { R_NONE = 0, R_DOT = 1, R_DOTNORM = 2, R_STEP = 3 };
 __host__ __device__ constexpr int red_values(int red) { return red == R_DOT ? 2 : red == R_DOTNORM ? 3 : red == R_STEP ? 5 : 0; }
 

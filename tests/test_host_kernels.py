@@ -11,7 +11,7 @@ CLANG = os.path.join(ROCM, "llvm", "bin", "clang++")
 
 
 @pytest.mark.skipif(not os.path.exists(CLANG), reason="clang not available")
-@pytest.mark.parametrize("name", ["inner_stop"])
+@pytest.mark.parametrize("name", ["inner_stop", "rho_updates", "rho_stencil"])
 def test_kernels_on_the_host(tmp_path, name):
     exe = tmp_path / name
     # (the launch functions of the sources are compiled with the kernels but never called)
