@@ -122,7 +122,9 @@ typedef struct {
     int inner_iters_total;    /* inner (Algorithm 2) iterations summed over all inner calls */
     int inner_calls;          /* calls of the inner solver */
     int restarts;             /* outer restarts from the true residual */
-    long dslash_count;        /* MULT applications (one D-hat_ee = 2 MULTs), any precision */
+    long dslash_count;        /* MULT applications that ran (one D-hat_ee = 2 MULTs), any precision:
+                                 with those of the D-hat that an inner solve may have applied
+                                 when it found that the step before had converged */
     int status;               /* same value as returned */
     double eo_rel_residual;   /* last recursive ||r_e|| / ||b-hat_e|| of the outer loop */
     double true_rel_residual; /* ||b - D x|| / ||b|| in FP64 on the full lattice */
@@ -414,7 +416,10 @@ int wc_link_grad(wc_lattice *lat, const void *lam_dev, const void *x_dev, double
 /* Per-kernel timing with HIP events on the lattice's stream.  While enabled, every
    launch of the hot kernels is bracketed by an event pair; wc_kernel_stats()
    synchronises and reports, for kernel slot k (0 <= k < wc_kernel_slots()), its
-   name, launch count, total milliseconds and total algorithmic bytes. */
+   name, launch count, total milliseconds and total algorithmic bytes.  Of an
+   inner solve, the launches of the iterations that Algorithm 2 does are reported:
+   those queued beyond the step at which it converged are left out, the ones that
+   returned at once and the one D-hat that may have run before the loop noticed. */
 int wc_set_timing(wc_lattice *lat, int enable);
 int wc_kernel_slots(void);
 int wc_kernel_stats(wc_lattice *lat, int slot, const char **name, long *launches,

@@ -181,6 +181,7 @@ template <int OP, int P, int XP> __global__ __launch_bounds__(kBlock) void k_vec
         if (stop != DONE_NO || !finite_c(al)) {
             if (first) {
                 c.fl[F_STOPPH] = stop != DONE_NO ? 2 : 1;
+                c.fl[F_RAN] = 1;
                 c.fl[kOut] = stop != DONE_NO ? stop : DONE_BREAK;
             }
             return;
@@ -225,6 +226,7 @@ template <int OP, int P, int XP> __global__ __launch_bounds__(kBlock) void k_vec
             if (first) {
                 if (!half) c.fl[F_ITERS] += 1;
                 c.fl[F_STOPPH] = half ? 1 : 2;
+                c.fl[F_RAN] = half ? 2 : 0;
                 c.fl[kOut] = half && isfinite(ss) ? DONE_HALF : DONE_BREAK;
             }
             return;
@@ -497,6 +499,7 @@ template <int N> __global__ __launch_bounds__(kBlock) void k_finalize(FinBatch B
         fl[F_DONE_A] = DONE_NO;
         fl[F_ITERS] = 0;
         fl[F_STOPPH] = 0;
+        fl[F_RAN] = 0;
         break;
     case FIN_CHECK: {
         const int stop = full_step_test(a[0], ld_c(sc, S_RHO0), sc[S_TOL2]);

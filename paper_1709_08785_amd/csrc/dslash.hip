@@ -1451,6 +1451,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(P == P64
         A.fl[F_DONE] = done;
         A.fl[F_ITERS] = it;
         A.fl[F_STOPPH] = stopph;
+        A.fl[F_RAN] = stopph == 1 ? 1 : 0;
     }
 }
 

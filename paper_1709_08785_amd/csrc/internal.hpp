@@ -40,7 +40,10 @@ enum ScalarSlot {
 // flags block (ints): done code, iterations completed
 // F_STOPPH: where the inner loop stopped: 1 at the half-step check (after the
 // first D-hat), 2 at the full-step check (after the second), 3 when a grid
-// barrier of the one-launch loop ran out of time (the call then fails)
+// barrier of the one-launch loop ran out of time (the call then fails).  The
+// launched loop takes either check one update later, when the next D-hat has run.
+// F_RAN: D-hats of the iteration after the F_ITERS counted ones that the loop
+// applied before it stopped
 // F_DONE and F_DONE_A: the done code.  The launched inner loop's two updates
 // raise it themselves, and other blocks of the same launch are then still to
 // read their guard.  So each update leaves the code in a word that its own
@@ -48,7 +51,7 @@ enum ScalarSlot {
 // and writes F_DONE_A, V_INNER_B reads F_DONE_A and writes F_DONE, and a kernel
 // between them reads what the update before it wrote.  All other loops, and the
 // host, use F_DONE alone.
-enum FlagSlot { F_DONE = 0, F_ITERS = 1, F_STOPPH = 2, F_DONE_A = 3, F_COUNT = 4 };
+enum FlagSlot { F_DONE = 0, F_ITERS = 1, F_STOPPH = 2, F_DONE_A = 3, F_RAN = 4, F_COUNT = 8 };
 enum DoneCode { DONE_NO = 0, DONE_FULL = 1, DONE_HALF = 2, DONE_BREAK = 4 };
 
 enum { NUM_LEVELS = 2 };  // 0 = inner loop, 1 = outer / FP64 loop
@@ -84,12 +87,13 @@ enum KernelSlot {
 };
 
 // One timed launch.  Inner-loop launches carry the iteration and phase they
-// belong to (phase 0: first D-hat and the s update, 1: second D-hat and the
-// x, r update, 2: the p update) and their algorithmic bytes split by system
-// (keyed by the system's flag block) and by lattice operator (keyed by the
-// flag blocks of the systems that share it), so that the work of systems
-// that had already converged -- those kernels return at once -- can be taken
-// out afterwards.
+// belong to (Algorithm 2: phase 0 the first D-hat and the s update, 1 the second
+// D-hat and the x, r, p update; the pipelined loop: inner_chunk_pipe) and their
+// algorithmic bytes split by system (keyed by the system's flag block) and by
+// lattice operator (keyed by the flag blocks of the systems that share it), so
+// that what lies beyond the (half) iteration at which a system converged can be
+// taken out afterwards: kernels that returned at once, and the D-hat that ran
+// before the stop was noticed.
 struct TimedPart {
     std::vector<const int *> owners;  // the part counts while any owner still runs
     double bytes;
@@ -100,7 +104,7 @@ struct TimedLaunch {
     hipEvent_t a, b;
     int iter = -1, phase = 0;
     std::vector<TimedPart> parts;
-    bool skipped = false;  // every system of the launch had stopped: no work done
+    bool skipped = false;  // every system of the launch had converged before it
 };
 
 // One linear system's device-side solver state: scalar and flag blocks per

@@ -444,7 +444,8 @@ int inner_solve(Run &R, const std::vector<int> &act, int src_id, int v_id) {
         if (all) break;
     }
     if (R.tl->timing) {
-        // launches queued after a system stopped did no work for it
+        // launches after the (half) iteration at which a system converged are
+        // not counted for it
         std::vector<StopPoint> stops;
         for (int k : act) {
             const SysState &st = *S_(R, k).st;
@@ -466,14 +467,12 @@ int inner_solve(Run &R, const std::vector<int> &act, int src_id, int v_id) {
         }
         s.info.inner_iters_total += iters;
         s.info.inner_calls += 1;
-        // MULTs done: four per full iteration, two for a half-step exit (the
-        // launches queued after the stop returned at once)
-        const int stopph = s.st->hf(L, F_STOPPH);
-        const long full = s.st->hf(L, F_ITERS);
+        // MULTs that ran: four per full iteration and what the loop applied
+        // after it (the launches queued after the stop returned at once)
+        const long full = s.st->hf(L, F_ITERS), ran = s.st->hf(L, F_RAN);
         // the pipelined loop also applies D-hat twice to set up, and its
         // half-step check comes before that iteration's D-hat
-        R.dslash[k] = dslash_before[k] + 4 * full +
-                      (R.pipe ? 4 : ((code != DONE_NO && stopph == 1) ? 2 : 0));
+        R.dslash[k] = dslash_before[k] + 4 * full + (R.pipe ? 4 : 2 * ran);
     }
     if (!fix.empty())
         if (int rc = vec_over(R, fix, R.pipe ? V_PIPE_FIX : V_INNER_FIX, P, [&](int k) {
