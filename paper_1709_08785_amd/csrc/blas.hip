@@ -22,9 +22,9 @@
 // A reduction is not finished by a kernel of its own: the update that consumes
 // it sums the partials in every block (in one order, so all blocks take the same
 // decisions), and block 0 records scalars and flags.  No kernel reads a word
-// that another block of it may be writing (FlagSlot for the done code).  From kFoldPartials partials on,
-// re-reading them in every block would cost more than it saves, and a fold
-// kernel first sums them once.  The convergence test of ||r||^2 is taken by the
+// that another block of it may be writing (FlagSlot for the done code).  On
+// larger lattices (worth_folding) re-reading the partials in every block would
+// cost more than it saves, and a fold kernel first sums them once.  The convergence test of ||r||^2 is taken by the
 // next V_INNER_A, or by FIN_CHECK before a host read; that of ||s||^2 by
 // V_INNER_B: up to a D-hat is done in vain once per inner solve, and the eleven
 // kernels of an iteration became six, or eight with the fold kernels.  Whole

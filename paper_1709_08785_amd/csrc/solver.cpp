@@ -189,15 +189,23 @@ double *partials(Run &R, int k, int slot) {
     return S_(R, k).st->partials + (size_t)slot * blocks_of(S_(R, k).lat->Vh, kMinBlock);
 }
 
-// From this many partials of one value on, a fold kernel sums them once instead
-// of every block of the next update.  The update's blocks each read all of them:
-// at 1024 (16^3x32) that is 40 KB a block and costs less than a launch, at
-// 5184 (24^3x48) it is 200 KB in each of 1296 blocks.
-constexpr int kFoldPartials = 1280;
+// Whether a fold kernel sums the n partials of one value once, instead of every
+// block of the next update of `bs` threads: when that reading takes longer than
+// a launch.  A thread has n / bs loads one after the other, and the more blocks
+// share a compute unit the longer they take; over block sizes and both stencil
+// forms (a partial per tile, or per block of the update's size) the line follows
+// n x blocks / bs^2.  us per inner iteration, without -> with the fold kernel, on
+// both sides of it: 64 threads FP32 256 tiles 49.8 -> 50.6, 384 tiles 60.2 -> 58.5,
+// 1024 tiles 103.6 -> 88.3; 128 threads 640 tiles 71.1 -> 71.0, 1024 tiles 91.1 ->
+// 88.5; 256 threads 1280 tiles 109.1 -> 111.6, 2000 tiles 144.7 -> 145.9, 2592 tiles
+// 179.0 -> 179.8, 3456 tiles 226.5 -> 223.1, 5184 tiles 330 -> 310; FP64 at 256
+// threads 2592 tiles 340.7 -> 343.8, 3456 tiles 475.8 -> 466.9; FP16 at 256 threads
+// (partials per block) 3456 tiles 153.1 -> 154.4, 5184 tiles 216.9 -> 212.4.
+bool worth_folding(int n, int blocks, int bs) { return (double)n * blocks >= 24.0 * bs * bs; }
 
 // the sources that the update after a reduction sums: the stencil's na values
 // (`stencil`) and the previous update's nb (`vec`), folded into the
-// scalar block first where some system has too many partials
+// scalar block first where that pays for some system
 int inner_sources(Run &R, const std::vector<int> &act, int stencil, int na, int vec, int nb, int guard, const int *ns,
                   SumSource *in0, SumSource *in1) {
     bool fold = false;
@@ -206,7 +214,7 @@ int inner_sources(Run &R, const std::vector<int> &act, int stencil, int na, int 
     for (int k : act) {
         in0[n] = SumSource{partials(R, k, stencil), ns[n]};
         in1[n] = SumSource{partials(R, k, vec), blocks_of(S_(R, k).lat->Vh, R.bs)};
-        fold = fold || in0[n].n >= kFoldPartials || in1[n].n >= kFoldPartials;
+        fold = fold || worth_folding(std::max(in0[n].n, in1[n].n), in1[n].n, launch_bs(R.bs));
         n++;
     }
     if (!fold) return WC_OK;
