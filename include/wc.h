@@ -180,8 +180,9 @@ int wc_tune_block_size(wc_lattice *lat, int prec, double us_per_pair[3], int *th
    the second half of D-hat_ee, eq. 8) of all systems on one lattice run in one
    launch that reads and rebuilds each link and loads each clover block once for
    all of them: a workgroup takes one 64-site tile and goes through the systems
-   with the operator in registers.  A few FP16 systems (fewer than 6 on a lattice
-   of more than 1024 tiles) are taken systems_per_thread at a time by each thread.
+   with the operator in registers.  Where that leaves much of the device idle
+   (some numbers of systems and tiles; FP16 systems more often, FP32 ones only at
+   systems_per_thread = 2), each thread takes systems_per_thread systems at a time.
    wc_set_multi_rhs: systems_per_thread = 2 or 4, 0 for one system per thread
    (each system's sites in workgroups of their own, the operator shared through
    the cache), or -1 (default) for 2 in FP32 and 4 in FP16.  WC_EINVAL for other

@@ -662,8 +662,7 @@ double mult_operator_bytes(int prec, int mode, int lr, int Vh) {
 // k_mult_mrhs: one thread takes one output site for G systems at once and applies
 // each link and clover block, loaded once, to all G.  A wavefront covers the 64
 // sites of one tile for one group of G systems, the waves of all groups of a tile
-// form one workgroup.  It remains for a few FP16 fields on large lattices
-// (multi_by_tile).
+// form one workgroup.  It remains where it is the faster one (multi_by_tile).
 // ---------------------------------------------------------------------------
 struct MrhsSys {
     void *out;
@@ -1079,16 +1078,43 @@ __global__ __launch_bounds__(64 * kMultiWaves) __attribute__((amdgpu_waves_per_e
     }
 }
 
-// Which form a launch takes.  k_mult_multi, except for FP16 storage with fewer
-// than 6 fields on more than 1024 tiles: a field's bytes are half as many there,
-// so fewer fields' neighbourhoods fit the L2, and k_mult_mrhs has more
-// wavefronts in flight (D-hat_ee, k_mult_mrhs -> k_mult_multi, us: 2 fields
-// 24^3x48 107 -> 138, 32^3x64 324 -> 392, but 16^3x32 36 -> 33; 6 fields 24^3x48
-// 294 -> 285; a 12-source solve at 8^4 9.1 -> 5.1 ms, at 20^3x32 69 -> 65).
-bool multi_by_tile(int prec, int ntiles, int nsys) { return prec == P32 || nsys >= 6 || ntiles <= kSplitTiles; }
+// Which form a launch takes.  1024 workgroups of k_mult_multi fit the device at
+// once, so its time grows in steps of 1024 tiles, and below 1024 it is that of its
+// longest workgroup; the workgroups of k_mult_mrhs are smaller and finish more
+// evenly.  D-hat_ee, us, k_mult_mrhs ->
+// k_mult_multi:
+//   FP32: k_mult_multi is up to 1.5 times faster (2592 tiles: 3 fields 164 -> 108,
+//   12 fields 399 -> 331), except for 2 fields, one wavefront a tile, in its second
+//   round (1152 tiles 43 -> 48, 1732 57 -> 63, but 1008 43 -> 35, 2400 84 -> 84), for 4
+//   fields just beyond 1024 tiles (1152 63 -> 70, but 1408 faster), and for 4, 6 or
+//   8 fields just beyond 512, from where on a workgroup takes all fields (640 tiles,
+//   8 fields 62 -> 65, but 7 fields at 704 66 -> 60 and 8 at 768 no slower).
+//   FP16, half the bytes and more arithmetic, needs full rounds: 384 tiles 12 | 16
+//   fields 64 -> 60 | 66 -> 74, 512 tiles 12 | 16 fields 64 -> 62 | 72 -> 78, 640 tiles 6 | 8 | 16 fields 61 ->
+//   58 | 64 -> 71 | 89 -> 127, 896 tiles 12 | 16 fields 91 -> 104 | 141 -> 134, 1008
+//   tiles 8 | 12 | 16 fields 73 -> 76 | 105 -> 106 | 151 -> 136, 1260 tiles 8 fields 88
+//   -> 113, 1732 tiles 8 | 12 fields 150 -> 139 | 182 -> 195, 2000 tiles 8 | 12 fields
+//   155 -> 146 | 226 -> 202, 2048 tiles 6 fields 120 -> 135, 2592 tiles 8 fields 190 ->
+//   197, 3024 tiles 8 | 12 fields 214 -> 212 | 330 -> 300, 5184 tiles 8 fields 383 ->
+//   365.  Few fields beyond 1024 tiles stay with k_mult_mrhs (2 fields 5184 tiles 107
+//   -> 138).  From 8192 tiles on a launch by itself loses 1-4% (16384 tiles, 12
+//   fields 1500 -> 1550), while the iterations of a solve gain (6575 -> 6400 us each).
+bool multi_by_tile(int prec, int ntiles, int nsys, int G, bool in_solve) {
+    if (prec == P32) {
+        if (G != 2) return true;
+        if (nsys == 2) return ntiles <= 1024 || ntiles > 1750;
+        if ((nsys == 4 || nsys == 6 || nsys == 8) && ntiles > 512 && ntiles <= 680) return false;
+        return !(nsys == 4 && ntiles > 1024 && ntiles <= 1200);
+    }
+    if (ntiles <= 512) return nsys < 15 || ntiles <= 341;
+    if (ntiles <= 1024) return nsys < 8 || (nsys >= 12 && ntiles >= 960) || (nsys >= 14 && ntiles >= 850);
+    if (nsys < 6) return false;
+    if (ntiles < 2700) return nsys <= 8 ? ntiles >= 1580 && ntiles <= 2010 : ntiles >= 1850 && ntiles <= 2030;
+    return in_solve || ntiles < 8192;
+}
 
 template <int P, int MODE, int RED, int LR> void launch_mrhs_lr(const MrhsArgs &A, hipStream_t s, int G) {
-    if (multi_by_tile(P, A.ntiles, A.nsys)) {
+    if (multi_by_tile(P, A.ntiles, A.nsys, G, A.s[0].done != nullptr)) {
         MrhsArgs B = A;
         // four workgroups fit a compute unit: fill them once, whole systems each
         // (two rounds of half as many systems: 16^3x32, 12 fields 50 -> 65 us)
@@ -1097,12 +1123,15 @@ template <int P, int MODE, int RED, int LR> void launch_mrhs_lr(const MrhsArgs &
         hipLaunchKernelGGL((k_mult_multi<P, MODE, RED, LR>), dim3(A.ntiles * B.ngroups), dim3(64 * kMultiWaves), 0, s, B);
         return;
     }
+    MrhsArgs B = A;
+    B.ngroups = (A.nsys + G - 1) / G;
     if constexpr (P == P16) {
-        MrhsArgs B = A;
-        B.ngroups = (A.nsys + G - 1) / G;
-        if (G == 2) hipLaunchKernelGGL((k_mult_mrhs<P, MODE, RED, LR, 2>), dim3(A.ntiles), dim3(64 * B.ngroups), 0, s, B);
-        else hipLaunchKernelGGL((k_mult_mrhs<P, MODE, RED, LR, 4>), dim3(A.ntiles), dim3(64 * B.ngroups), 0, s, B);
+        if (G != 2) {
+            hipLaunchKernelGGL((k_mult_mrhs<P, MODE, RED, LR, 4>), dim3(A.ntiles), dim3(64 * B.ngroups), 0, s, B);
+            return;
+        }
     }
+    hipLaunchKernelGGL((k_mult_mrhs<P, MODE, RED, LR, 2>), dim3(A.ntiles), dim3(64 * B.ngroups), 0, s, B);
 }
 
 template <int P, int MODE, int RED> void launch_mrhs_mode(const MrhsArgs &A, hipStream_t s, int lr, int G) {
