@@ -200,8 +200,15 @@ double *partials(Run &R, int k, int slot) {
 // 88.5; 256 threads 1280 tiles 109.1 -> 111.6, 2000 tiles 144.7 -> 145.9, 2592 tiles
 // 179.0 -> 179.8, 3456 tiles 226.5 -> 223.1, 5184 tiles 330 -> 310; FP64 at 256
 // threads 2592 tiles 340.7 -> 343.8, 3456 tiles 475.8 -> 466.9; FP16 at 256 threads
-// (partials per block) 3456 tiles 153.1 -> 154.4, 5184 tiles 216.9 -> 212.4.
-bool worth_folding(int n, int blocks, int bs) { return (double)n * blocks >= 24.0 * bs * bs; }
+// (partials per block) 3456 tiles 153.1 -> 154.4, 5184 tiles 216.9 -> 212.4.  The
+// blocks of a batch's other systems count too, up to four systems (further ones
+// wait for a compute unit either way); FP32 at 256 threads, 2 systems 1280 tiles
+// 159.6 -> 162.6, 2592 tiles 308 -> 300, 4 systems 1024 tiles 189.3 -> 194.1, 1600
+// tiles 315.7 -> 313.5, 12 systems 1024 tiles 455.6 -> 457.1, 1280 tiles 633 -> 628,
+// FP16 1280 tiles 562 -> 551, 2000 tiles 780 -> 750.
+bool worth_folding(int n, int blocks, int systems, int bs) {
+    return (double)n * blocks * std::min(systems, 4) >= 24.0 * bs * bs;
+}
 
 // the sources that the update after a reduction sums: the stencil's na values
 // (`stencil`) and the previous update's nb (`vec`), folded into the
@@ -214,7 +221,7 @@ int inner_sources(Run &R, const std::vector<int> &act, int stencil, int na, int 
     for (int k : act) {
         in0[n] = SumSource{partials(R, k, stencil), ns[n]};
         in1[n] = SumSource{partials(R, k, vec), blocks_of(S_(R, k).lat->Vh, R.bs)};
-        fold = fold || worth_folding(std::max(in0[n].n, in1[n].n), in1[n].n, launch_bs(R.bs));
+        fold = fold || worth_folding(std::max(in0[n].n, in1[n].n), in1[n].n, (int)act.size(), launch_bs(R.bs));
         n++;
     }
     if (!fold) return WC_OK;

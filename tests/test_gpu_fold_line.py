@@ -2,8 +2,9 @@
 blocks, a fold kernel sums them once.  The line lies at 314 tiles for blocks of 64
 threads and at 887 for 128 (1255 with FP16 storage, whose stencil then leaves a
 partial per block), and at 2508 for 256.  Solves just below and above it against
-the oracle's true residual, with exact iteration counts, and a batch with one
-system on either side."""
+the oracle's true residual, with exact iteration counts, and batches: several small
+systems with one that needs the kernel, and systems (up to four count) that need it
+together and not alone."""
 import numpy as np
 import pytest
 
@@ -57,9 +58,11 @@ def test_solve_on_both_sides(threads, inner, dims):
 
 
 @pytest.mark.parametrize("inner", [wc.FP32, wc.FP16])
-def test_batch_across_the_line(inner):
-    lats, Us, bs = zip(*(lattice(d, s, 64) for d, s in (((8, 8, 8, 8), 1981), ((12, 14, 20, 12), 1982))))
-    xs, infos = wc.solve_multi(lats, [dev(b) for b in bs], [KAPPA] * 2, [1.0] * 2, 1e-12, inner_prec=inner)
+@pytest.mark.parametrize("dims", [((8, 8, 8, 8), (12, 14, 20, 12)), ((12, 12, 12, 12),) * 2, ((12, 12, 12, 16),) * 2,
+                                  ((12, 12, 12, 12),) * 4])
+def test_batch_across_the_line(inner, dims):
+    lats, Us, bs = zip(*(lattice(d, 1981 + k, 64) for k, d in enumerate(dims)))
+    xs, infos = wc.solve_multi(lats, [dev(b) for b in bs], [KAPPA] * len(lats), [1.0] * len(lats), 1e-12, inner_prec=inner)
     for U, b, x, info in zip(Us, bs, xs, infos):
         r, bn = oracle.residual(U, KAPPA, 1.0, b, x.cpu().numpy())
         say(inner, info["inner_iters_total"], r / bn)
