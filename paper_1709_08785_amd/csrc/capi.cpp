@@ -882,11 +882,13 @@ int tune_block_size(wc_lattice *lat, int prec, double us[3], int *chosen) {
         if (which & 1) {
             MultCall c1 = mult_call(prec, M_HOPINV, 1, buf + sb, buf, nullptr, 0.0);
             c1.bs = bs;
+            c1.loop = true;
             if (int r = launch_mult(lat, c1)) return r;
         }
         if (which & 2) {
             MultCall c2 = mult_call(prec, M_DHAT, 0, buf + 2 * sb, buf + sb, buf, -lat->kappa * lat->kappa);
             c2.bs = bs;
+            c2.loop = true;
             c2.red = R_DOT;
             c2.aux = buf;
             c2.red_to = RedTarget{lat->sys.partials, (double *)(buf + 3 * sb)};

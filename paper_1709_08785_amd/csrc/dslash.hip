@@ -229,7 +229,12 @@ __device__ __forceinline__ void hop_dir(const MultKArgs &a, const SiteCoord &c, 
 // 12x14x10x18 67.8 -> 63.1, 20^3x40 (184 MB) 352 -> 332, 24^3x48 (382 MB) 679 ->
 // 697; FP16 24^3x48 (64 MB) 219 -> 214, 32^3x48 (151 MB) 417 -> 384.  The
 // multi-system kernel reads a link once for all its systems and gained nothing.
-constexpr double kKeepLinkBytes = 192e6;
+// Reconstruct-8 links keep to it in a solve (us per iteration 32^4 (134 MB) 448 ->
+// 429, 28^2x32x48 (154 MB) 528 -> 505), but a launch by itself, with fewer waves
+// in flight than the other forms, gains only up to kKeepLinkBytes8: D-hat_ee
+// 24^3x48 (85 MB) 106.6 -> 104.2, 24^2x32x48 (113 MB) 133 -> 132, 32^4 150 -> 155,
+// 28^2x32x48 180 -> 183.
+constexpr double kKeepLinkBytes = 192e6, kKeepLinkBytes8 = 120e6;
 enum OperatorReads { SHARED = 0, KEEP = 1, STREAM = 2 };
 // The one-system FP16 MULT and D-hat instances are held to four waves per
 // SIMD (128 VGPRs; they use about 103 with both hops' loads in flight, hop_dir).
@@ -684,6 +689,7 @@ struct MrhsArgs {
     int ngroups;  // groups of systems (k_mult_mrhs: of G systems, ceil(nsys / G))
     int ntiles;   // 64-site tiles of one parity
     int chunk;    // workgroups per XCD chunk of the block remap (0: one slab per XCD)
+    bool loop;    // MultCall::loop
     MrhsSys s[kMaxSys];
 };
 
@@ -1114,7 +1120,7 @@ bool multi_by_tile(int prec, int ntiles, int nsys, int G, bool in_solve) {
 }
 
 template <int P, int MODE, int RED, int LR> void launch_mrhs_lr(const MrhsArgs &A, hipStream_t s, int G) {
-    if (multi_by_tile(P, A.ntiles, A.nsys, G, A.s[0].done != nullptr)) {
+    if (multi_by_tile(P, A.ntiles, A.nsys, G, A.loop)) {
         MrhsArgs B = A;
         // four workgroups fit a compute unit: fill them once, whole systems each
         // (two rounds of half as many systems: 16^3x32, 12 fields 50 -> 65 us)
@@ -1501,6 +1507,7 @@ static int launch_mult_mrhs(hipStream_t s, const MultCall *calls, int n, wc_latt
     A.coef = c0.coef;
     A.nsys = n;
     A.ngroups = 0;  // set with the form
+    A.loop = c0.loop;
     A.ntiles = blocks_of(lat->Vh, 64);
     A.chunk = lattice_chunk(lat, c0.prec);
     double bytes = mult_operator_bytes(c0.prec, c0.mode, lr, lat->Vh);
@@ -1653,7 +1660,7 @@ int launch_mult_batch(hipStream_t s, const MultCall *calls, int n, wc_lattice *t
     }
     const unsigned lds = B.h.interleave ? 0u : cap_lds_bytes(c0.lat, c0.prec, split ? 64 * kSplitWaves : bs, c0.mode);
     const int shape = split ? kSplitBlock : bs;
-    const bool keep = link_bytes <= kKeepLinkBytes;
+    const bool keep = link_bytes <= (lr == 8 && !c0.loop ? kKeepLinkBytes8 : kKeepLinkBytes);
     if (c0.prec == P64) dispatch_mode<P64>(B, c0.mode, c0.red, blocks, shape, lds, s, 12, keep);
     else if (c0.prec == P32) dispatch_mode<P32>(B, c0.mode, c0.red, blocks, shape, lds, s, lr, keep);
     else dispatch_mode<P16>(B, c0.mode, c0.red, blocks, shape, lds, s, 12, keep);

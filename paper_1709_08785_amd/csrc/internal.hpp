@@ -432,6 +432,7 @@ struct MultCall {
     RedTarget red_to;
     const int *done;     // skip this call when *done != 0
     int bs;              // threads per block of the launch (64, 128 or 256; 0 = 256)
+    bool loop;           // one of an inner loop's launches, or of the timings that stand for them
 };
 // timing_lat (default: the first call's lattice) receives the timing record
 int launch_mult_batch(hipStream_t s, const MultCall *calls, int n, wc_lattice *timing_lat = nullptr);

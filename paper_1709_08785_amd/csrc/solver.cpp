@@ -117,6 +117,7 @@ int dhat(Run &R, const std::vector<int> &act, int prec, int out_id, int in_id, i
     if (int rc = mult_over(R, act, [&](int k) {
             MultCall c = mc(R, k, prec, M_HOPINV, 1, W(R, k, tmp_id), W(R, k, in_id), nullptr, 0.0);
             c.done = guarded ? S_(R, k).st->fl(lvl) : nullptr;
+            c.loop = guarded;
             return c;
         }))
         return rc;
@@ -128,6 +129,7 @@ int dhat(Run &R, const std::vector<int> &act, int prec, int out_id, int in_id, i
         c.aux = aux_id >= 0 ? W(R, k, aux_id) : nullptr;
         c.red_to = RedTarget{s.st->partials, s.st->sc(lvl) + slot};
         c.done = guarded ? s.st->fl(lvl) : nullptr;
+        c.loop = guarded;
         return c;
     });
 }
@@ -243,6 +245,7 @@ int inner_dhat(Run &R, const std::vector<int> &act, int out_id, int in_id, int r
     if (int rc = mult_over(R, act, [&](int k) {
             MultCall c = mc(R, k, P, M_HOPINV, 1, W(R, k, W_ITMP), W(R, k, in_id), nullptr, 0.0);
             c.done = S_(R, k).st->fl(L) + guard;
+            c.loop = true;
             return c;
         }))
         return rc;
@@ -256,6 +259,7 @@ int inner_dhat(Run &R, const std::vector<int> &act, int out_id, int in_id, int r
         c.aux = W(R, k, W_IRT);
         c.red_to = RedTarget{partials(R, k, slot), nullptr};
         c.done = s.st->fl(L) + guard;
+        c.loop = true;
         calls[n++] = c;
         R.dslash[k]++;
     }
