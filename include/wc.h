@@ -230,9 +230,10 @@ int wc_wave_cap(const wc_lattice *lat, int prec, int dhat);
 
 /* Process-wide file in which the launch-shape tuner keeps its results, one
    line per device (architecture and compute units), lattice extents,
-   precision, FP32 link form and pinned wave cap (wc_set_wave_cap); a later
+   precision, FP32 link form and pinned wave cap (wc_set_wave_cap), with the form
+   of the stencil that was timed (wc_set_block_size) at its end; a later
    tuning of the same case, in this process or another, takes the stored
-   shape instead of timing.  Tunings under a pinned block size or XCD chunk
+   shape instead of timing, if it is of the form that the lattice uses.  Tunings under a pinned block size or XCD chunk
    do not use the file.  path NULL or
    "" (the default) keeps no file.  A file that cannot be read or written only
    costs a new timing.  The path is copied. */

@@ -759,8 +759,10 @@ static std::string tune_key(const wc_lattice *lat, int prec) {
 }
 
 // the last entry for key in the cache file: block size, chunk, wave caps of
-// the two kernel classes, microseconds per pair at the block sizes 64, 128, 256
-static bool tune_lookup(const std::string &key, int *bs, int *chunk, int caps[2], double us[3]) {
+// the two kernel classes, microseconds per pair at the block sizes 64, 128, 256,
+// and the form of the stencil it was timed on (split: 1; entries without the field
+// are of one thread per site).  Only an entry of the form at hand counts.
+static bool tune_lookup(const std::string &key, bool split, int *bs, int *chunk, int caps[2], double us[3]) {
     std::lock_guard<std::mutex> g(g_tune_mu);
     if (g_tune_cache.empty()) return false;
     std::FILE *f = std::fopen(g_tune_cache.c_str(), "r");
@@ -770,10 +772,10 @@ static bool tune_lookup(const std::string &key, int *bs, int *chunk, int caps[2]
     const std::string head = "wc-tune-v3 " + key + " ";
     while (std::fgets(line, sizeof(line), f)) {
         if (std::strncmp(line, head.c_str(), head.size()) != 0) continue;
-        int b = 0, c = -1, w0 = -1, w1 = -1;
+        int b = 0, c = -1, w0 = -1, w1 = -1, form = 0;
         double u[3] = {0, 0, 0};
-        if (std::sscanf(line + head.size(), "%d %d %d %d %lf %lf %lf", &b, &c, &w0, &w1, &u[0], &u[1], &u[2]) == 7 &&
-            valid_block_size(b) && c >= 0 && valid_wave_cap(w0) && valid_wave_cap(w1)) {
+        if (std::sscanf(line + head.size(), "%d %d %d %d %lf %lf %lf %d", &b, &c, &w0, &w1, &u[0], &u[1], &u[2], &form) >= 7 &&
+            form == (split ? 1 : 0) && valid_block_size(b) && c >= 0 && valid_wave_cap(w0) && valid_wave_cap(w1)) {
             *bs = b;
             *chunk = c;
             caps[0] = w0;
@@ -786,25 +788,23 @@ static bool tune_lookup(const std::string &key, int *bs, int *chunk, int caps[2]
     return found;
 }
 
-static void tune_store(const std::string &key, int bs, int chunk, const int caps[2], const double us[3]) {
+static void tune_store(const std::string &key, bool split, int bs, int chunk, const int caps[2], const double us[3]) {
     std::lock_guard<std::mutex> g(g_tune_mu);
     if (g_tune_cache.empty()) return;
     std::FILE *f = std::fopen(g_tune_cache.c_str(), "a");
     if (!f) return;  // a cache that cannot be written only costs a later tuning
-    std::fprintf(f, "wc-tune-v3 %s %d %d %d %d %.3f %.3f %.3f\n", key.c_str(), bs, chunk, caps[0], caps[1], us[0], us[1],
-                 us[2]);
+    std::fprintf(f, "wc-tune-v3 %s %d %d %d %d %.3f %.3f %.3f %d\n", key.c_str(), bs, chunk, caps[0], caps[1], us[0],
+                 us[1], us[2], split ? 1 : 0);
     std::fclose(f);
 }
 
 // take the stored shape of a case, if the cache file has it
 static bool stored_shape(wc_lattice *lat, int prec, const std::string &key, double us[3]) {
     int b = 0, c = -1, w[2] = {-1, -1};
-    if (!tune_lookup(key, &b, &c, w, us)) return false;
+    if (!tune_lookup(key, split_stencil(lat, prec), &b, &c, w, us)) return false;
     lat->bs_tuned[prec] = b;
     lat->chunk_tuned[prec] = c;
-    // a file may hold caps that were timed on another form of the stencil
-    const bool split = split_stencil(lat, prec);
-    for (int k = 0; k < 2; k++) lat->cap_tuned[prec][k] = split ? default_wave_cap(prec) : w[k];
+    for (int k = 0; k < 2; k++) lat->cap_tuned[prec][k] = w[k];
     lat->gen++;
     return true;
 }
@@ -1028,7 +1028,7 @@ int tune_block_size(wc_lattice *lat, int prec, double us[3], int *chosen) {
     if (us)
         for (int c = 0; c < 3; c++) us[c] = u[c];
     if (chosen) *chosen = cand[best % 3];
-    if (use_cache) tune_store(key, cand[best % 3], chunks[h], caps, u);
+    if (use_cache) tune_store(key, split_stencil(lat, prec), cand[best % 3], chunks[h], caps, u);
     return WC_OK;
 }
 
