@@ -412,7 +412,7 @@ template <int P, int MODE, int RED, int OPR, int LR>
 __global__ __launch_bounds__(64 * kSplitWaves) __attribute__((amdgpu_waves_per_eu(split_waves<P, MODE, LR>())))
 void k_mult_split(MultBatch B) {
     using R = typename Real<P>::T;
-    __shared__ cx<R> part[kSplitWaves][12][64];
+    __shared__ alignas(16) cx<R> part[kSplitWaves][12][64];  // M_DCANON: sites of double2 as well
     __shared__ cx<R> yb[2][6][64];
     __shared__ float mx[2][64];
     int s, lb;
@@ -514,6 +514,7 @@ void k_mult_split(MultBatch B) {
     if constexpr (MODE == M_DCANON) {
         // through LDS, so that the canonical sites leave as whole 192-byte pieces
         double2(*st)[13] = reinterpret_cast<double2(*)[13]>(part);  // 13: as kPadSpin in layout.hip
+        static_assert(sizeof(part) >= 64 * sizeof(*st), "the sites of a tile fit the hops' sums");
         if (site) {
 #pragma unroll
             for (int k = 0; k < 6; k++) st[lane][6 * w + k] = make_double2((double)out[k].re, (double)out[k].im);
