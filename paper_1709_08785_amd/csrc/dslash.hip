@@ -412,7 +412,7 @@ template <int P, int MODE, int RED, int OPR, int LR>
 __global__ __launch_bounds__(64 * kSplitWaves) __attribute__((amdgpu_waves_per_eu(split_waves<P, MODE, LR>())))
 void k_mult_split(MultBatch B) {
     using R = typename Real<P>::T;
-    __shared__ alignas(16) cx<R> part[kSplitWaves][12][64];  // M_DCANON: sites of double2 as well
+    alignas(16) __shared__ cx<R> part[kSplitWaves][12][64];  // M_DCANON: sites of double2 as well
     __shared__ cx<R> yb[2][6][64];
     __shared__ float mx[2][64];
     int s, lb;
