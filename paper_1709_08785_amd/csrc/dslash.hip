@@ -1088,17 +1088,16 @@ __global__ __launch_bounds__(64 * kMultiWaves) __attribute__((amdgpu_waves_per_e
 // Which form a launch takes.  1024 workgroups of k_mult_multi fit the device at
 // once, so its time grows in steps of 1024 tiles, and below 1024 it is that of its
 // longest workgroup; the workgroups of k_mult_mrhs are smaller and finish more
-// evenly.  D-hat_ee, us, k_mult_mrhs ->
-// k_mult_multi:
+// evenly.  D-hat_ee, us, k_mult_mrhs -> k_mult_multi:
 //   FP32: k_mult_multi is up to 1.5 times faster (2592 tiles: 3 fields 164 -> 108,
 //   12 fields 399 -> 331), except for 2 fields, one wavefront a tile, in its second
-//   round (1152 tiles 43 -> 48, 1732 57 -> 63, but 1008 43 -> 35, 2400 84 -> 84), for 4
-//   fields just beyond 1024 tiles (1152 63 -> 70, but 1408 faster), and for 4, 6 or
-//   8 fields just beyond 512, from where on a workgroup takes all fields (640 tiles,
+//   round and a little beyond (1152 tiles 43 -> 48, 1732 57 -> 63, 2079 73 -> 76, but 1008
+//   43 -> 35, 2376 82 -> 83, 2592 103 -> 89), for 4 fields just beyond 1024 tiles
+//   (1152 63 -> 70, but 1408 faster), and for 4, 6 or 8 fields just beyond 512, from where on a workgroup takes all fields (640 tiles,
 //   8 fields 62 -> 65, but 7 fields at 704 66 -> 60 and 8 at 768 no slower).
 //   FP16, half the bytes and more arithmetic, needs full rounds: 384 tiles 12 | 16
-//   fields 64 -> 60 | 66 -> 74, 512 tiles 12 | 16 fields 64 -> 62 | 72 -> 78, 640 tiles 6 | 8 | 16 fields 61 ->
-//   58 | 64 -> 71 | 89 -> 127, 896 tiles 12 | 16 fields 91 -> 104 | 141 -> 134, 1008
+//   fields 64 -> 60 | 66 -> 74, 512 tiles 12 | 16 fields 64 -> 62 | 72 -> 78, 640 tiles
+//   6 | 8 | 16 fields 61 -> 58 | 64 -> 71 | 89 -> 127, 896 tiles 12 | 16 fields 91 -> 104 | 141 -> 134, 1008
 //   tiles 8 | 12 | 16 fields 73 -> 76 | 105 -> 106 | 151 -> 136, 1260 tiles 8 fields 88
 //   -> 113, 1732 tiles 8 | 12 fields 150 -> 139 | 182 -> 195, 2000 tiles 8 | 12 fields
 //   155 -> 146 | 226 -> 202, 2048 tiles 6 fields 120 -> 135, 2592 tiles 8 fields 190 ->
@@ -1109,7 +1108,7 @@ __global__ __launch_bounds__(64 * kMultiWaves) __attribute__((amdgpu_waves_per_e
 bool multi_by_tile(int prec, int ntiles, int nsys, int G, bool in_solve) {
     if (prec == P32) {
         if (G != 2) return true;
-        if (nsys == 2) return ntiles <= 1024 || ntiles > 1750;
+        if (nsys == 2) return ntiles <= 1024 || ntiles > 2304;
         if ((nsys == 4 || nsys == 6 || nsys == 8) && ntiles > 512 && ntiles <= 680) return false;
         return !(nsys == 4 && ntiles > 1024 && ntiles <= 1200);
     }

@@ -26,8 +26,8 @@ LINES = [
     ((16, 16, 16, 24), wc.FP32, (12,), (4, 8)),                 # 768
     ((14, 16, 18, 34), wc.FP32, (12, 8, 18), (2, 4)),           # 1071
     ((14, 16, 20, 36), wc.FP32, (12,), (2, 4)),                 # 1260
-    ((14, 18, 20, 44), wc.FP32, (12,), (2,)),                   # 1732
-    ((12, 20, 24, 40), wc.FP32, (12,), (2,)),                   # 1800
+    ((16, 16, 16, 72), wc.FP32, (12,), (2,)),                   # 2304
+    ((12, 24, 24, 44), wc.FP32, (12,), (2,)),                   # 2376
     ((14, 14, 14, 16), wc.FP16, (12,), (2, 15)),                # 343
     ((16, 16, 16, 10), wc.FP16, (12,), (15,)),                  # 320
     ((16, 16, 16, 16), wc.FP16, (12,), (14, 15)),               # 512
