@@ -155,7 +155,7 @@ void wc_solve_params_default(wc_solve_params *p);
    odd parity, then the D-hat half with its fused dot; Sec. II-B eq. 8) on
    zero vectors at 64, 128 and 256 threads and at XCD chunks of 8, 16, 32 and
    64 tiles (wc_set_xcd_chunk; only the pinned one when pinned) and keeps the
-   fastest shape; 256 threads (64 on lattices of up to 256 tiles, where the
+   fastest shape; 256 threads (64 on lattices of up to 256 or 1025 to 1280 tiles, where the
    stencil does not depend on it) at chunk 32 are displaced only by a shape at
    least 3% faster, in the sweep and again in three alternating timings
    against it.  With a pinned block size, the chunk and caps are chosen

@@ -811,9 +811,15 @@ static bool stored_shape(wc_lattice *lat, int prec, const std::string &key, doub
 
 // The vector kernels' block size where the split stencil leaves it to them: 64
 // threads while that gives every compute unit at most one block (FP64
-// 12x14x10x18: 67.3 us an inner iteration against 69.2 at 256), 256 above
-// (16^4: 69.7 against 75.9 at 64).
-static int split_block_size(const wc_lattice *lat) { return pad_sites(lat->Vh) / kTile <= 256 ? 64 : 256; }
+// 12x14x10x18: 67.3 us an inner iteration against 69.2 at 256), and where blocks
+// of 256 would be one or a few more than the compute units (1152 tiles: 103.5
+// against 104.2, FP64 177.8 against 182.0, pipelined 114.0 against 118.9), 256
+// elsewhere (16^4: 69.7 against 75.9 at 64; 1408 tiles: 116.1 against 116.3, batches
+// of 2 169 against 171).
+static int split_block_size(const wc_lattice *lat) {
+    const int tiles = pad_sites(lat->Vh) / kTile;
+    return tiles <= 256 || (tiles > 1024 && tiles <= 1280) ? 64 : 256;
+}
 
 // The launch shape of a lattice's first solve.  For the split stencil it follows
 // from the lattice: no wave cap gained anything at any size from 8^4 to 48^3x96

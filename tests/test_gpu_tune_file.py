@@ -74,3 +74,10 @@ def test_site_form_takes_old_entries(tmp_path, form, taken):
         assert (shape == (128, 0)) == taken
     finally:
         wc.set_tune_cache(None)
+
+
+@pytest.mark.parametrize("dims,threads", [((16, 16, 16, 8), 64), ((12, 12, 12, 20), 256), ((16, 16, 16, 32), 256),
+                                          ((14, 16, 18, 34), 64), ((16, 16, 20, 32), 64), ((16, 16, 16, 42), 256)])
+def test_first_shape_follows_the_lattice(dims, threads):
+    # 256, 270, 1024, 1071, 1280 and 1344 tiles
+    assert first_solve(dims, wc.FP32) == (threads, 64 if dims[3] * dims[0] * dims[1] * dims[2] <= 1024 * 128 else 32)
