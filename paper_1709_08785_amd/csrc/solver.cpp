@@ -489,9 +489,11 @@ int inner_solve(Run &R, const std::vector<int> &act, int src_id, int v_id) {
         // MULTs that ran: four per full iteration and what the loop applied
         // after it (the launches queued after the stop returned at once)
         const long full = s.st->hf(L, F_ITERS), ran = s.st->hf(L, F_RAN);
-        // the pipelined loop also applies D-hat twice to set up, and its
-        // half-step check comes before that iteration's D-hat
-        R.dslash[k] = dslash_before[k] + 4 * full + (R.pipe ? 4 : 2 * ran);
+        // the pipelined loop's half-step check comes before that iteration's
+        // D-hats and its full-step check between them (its two D-hats to set up
+        // are in dslash_before)
+        const bool mid = code != DONE_NO && s.st->hf(L, F_STOPPH) == 2;
+        R.dslash[k] = dslash_before[k] + 4 * full + (R.pipe ? (mid ? -2 : 0) : 2 * ran);
     }
     if (!fix.empty())
         if (int rc = vec_over(R, fix, R.pipe ? V_PIPE_FIX : V_INNER_FIX, P, [&](int k) {

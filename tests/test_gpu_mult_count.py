@@ -48,3 +48,29 @@ def test_mults_that_ran(inner, graph):
     # exits of both kinds occur among these solves
     assert 0 < sum(extra[500]) < 2 * calls
     lat.close()
+
+
+@pytest.mark.parametrize("every", [1, 500])
+def test_mults_that_ran_in_the_pipelined_loop(every):
+    # two D-hats to set up, two per iteration; a half-step exit comes before both
+    # of its iteration's, a full-step exit between them
+    dims = (8, 8, 8, 8)
+    lat = wc.Lattice(dims)
+    lat.load_links(dev(synth.random_links(dims, 0.3, 1971)))
+    extra, calls = 0, 0
+    for seed in range(4):
+        b = dev(synth.gaussian_source(dims, 2975 + seed))
+        _, info = lat.solve(b, 0.13, 1.0, 1e-10, inner_method=1, check_every=every)
+        assert info["restarts"] == 0
+        e = info["dslash_count"] - 5 - 2 * info["inner_calls"] - 4 * info["inner_iters_total"]
+        assert e % 2 == 0 and 0 <= e <= 2 * info["inner_calls"]
+        extra += e
+        calls += info["inner_calls"]
+    say(every, extra, calls)
+    assert 0 < extra < 2 * calls
+    # stopped by the iteration cap: nothing is left out
+    _, info = lat.solve(b, 0.13, 1.0, 1e-10, inner_method=1, check_every=every, fixed_work=5, outer_maxit=1,
+                        raise_on_error=False)
+    rest = info["dslash_count"] - info["inner_calls"] * (4 + 4 * 5 + 2)
+    assert rest == 5
+    lat.close()
