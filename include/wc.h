@@ -418,10 +418,10 @@ int wc_link_grad(wc_lattice *lat, const void *lam_dev, const void *x_dev, double
 /* Per-kernel timing with HIP events on the lattice's stream.  While enabled, every
    launch of the hot kernels is bracketed by an event pair; wc_kernel_stats()
    synchronises and reports, for kernel slot k (0 <= k < wc_kernel_slots()), its
-   name, launch count, total milliseconds and total algorithmic bytes.  Of an
-   inner solve, the launches of the iterations that Algorithm 2 does are reported:
-   those queued beyond the step at which it converged are left out, the ones that
-   returned at once and the one D-hat that may have run before the loop noticed. */
+   name, launch count, total milliseconds and total algorithmic bytes.  Launches
+   that an inner solve queued after its loop had stopped return at once and are
+   left out; the D-hat that may have run before the loop noticed that the step
+   before had converged (dslash_count) is among the reported ones. */
 int wc_set_timing(wc_lattice *lat, int enable);
 int wc_kernel_slots(void);
 int wc_kernel_stats(wc_lattice *lat, int slot, const char **name, long *launches,

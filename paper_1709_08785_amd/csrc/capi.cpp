@@ -187,7 +187,7 @@ struct SlotStats {
 static int collect_stats(wc_lattice *lat, SlotStats *st) {
     WC_HIP(hipStreamSynchronize(lat->stream));
     for (auto &t : lat->launches) {
-        if (t.skipped) continue;  // converged systems only
+        if (t.skipped) continue;  // stopped systems only: the kernel returned at once
         float ms = 0.f;
         WC_HIP(hipEventElapsedTime(&ms, t.a, t.b));
         st[t.slot].n++;

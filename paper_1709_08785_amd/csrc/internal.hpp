@@ -87,13 +87,11 @@ enum KernelSlot {
 };
 
 // One timed launch.  Inner-loop launches carry the iteration and phase they
-// belong to (Algorithm 2: phase 0 the first D-hat and the s update, 1 the second
-// D-hat and the x, r, p update; the pipelined loop: inner_chunk_pipe) and their
-// algorithmic bytes split by system (keyed by the system's flag block) and by
-// lattice operator (keyed by the flag blocks of the systems that share it), so
-// that what lies beyond the (half) iteration at which a system converged can be
-// taken out afterwards: kernels that returned at once, and the D-hat that ran
-// before the stop was noticed.
+// belong to (inner_chunk, inner_chunk_pipe) and their algorithmic bytes split by
+// system (keyed by the system's flag block) and by lattice operator (keyed by the
+// flag blocks of the systems that share it), so that the work of systems whose
+// loop had stopped -- those kernels return at once -- can be taken out
+// afterwards.
 struct TimedPart {
     std::vector<const int *> owners;  // the part counts while any owner still runs
     double bytes;
@@ -104,7 +102,7 @@ struct TimedLaunch {
     hipEvent_t a, b;
     int iter = -1, phase = 0;
     std::vector<TimedPart> parts;
-    bool skipped = false;  // every system of the launch had converged before it
+    bool skipped = false;  // every system of the launch had stopped: no work done
 };
 
 // One linear system's device-side solver state: scalar and flag blocks per

@@ -282,8 +282,8 @@ int inner_chunk(Run &R, const std::vector<int> &act, int n, int base = 0) {
         v.partials = partials(R, act[j], slot);
         return v;
     };
-    // tags for the timing records: iteration and phase (0: first D-hat and the
-    // s update, 1: second D-hat and the x, r, p update)
+    // tags for the timing records: iteration and phase (0: first D-hat, 1: s
+    // update, 2: second D-hat, 3: x, r, p update)
     auto tag = [&](int it, int ph) {
         R.tl->tag_iter = it;
         R.tl->tag_phase = ph;
@@ -293,13 +293,15 @@ int inner_chunk(Run &R, const std::vector<int> &act, int n, int base = 0) {
         if (int rc = inner_dhat(R, act, W_IQ, W_IP, R_DOT, PS_RQ, F_DONE, ns)) return rc;
         if (int rc = inner_sources(R, act, PS_RQ, 2, PS_RR, 1, F_DONE, ns, in0, in1)) return rc;
         int i = 0;
+        tag(base + j, 1);
         if (int rc = vec_over(R, act, V_INNER_A, P,
                               [&](int k) { return update(i++, PS_SS, vc(R, k, L, W(R, k, W_IR), W(R, k, W_IQ), W(R, k, W_IRT))); }))
             return rc;
-        tag(base + j, 1);
+        tag(base + j, 2);
         if (int rc = inner_dhat(R, act, W_IT, W_IR, R_STEP, PS_STEP, F_DONE_A, ns)) return rc;
         if (int rc = inner_sources(R, act, PS_STEP, 5, PS_SS, 3, F_DONE_A, ns, in0, in1)) return rc;
         i = 0;
+        tag(base + j, 3);
         if (int rc = vec_over(R, act, V_INNER_B, P, [&](int k) {
                 return update(i++, PS_RR, vc(R, k, L, W(R, k, W_IX), W(R, k, W_IR), W(R, k, W_IP), W(R, k, W_IT),
                                              W(R, k, W_IQ)));
@@ -463,15 +465,15 @@ int inner_solve(Run &R, const std::vector<int> &act, int src_id, int v_id) {
         if (all) break;
     }
     if (R.tl->timing) {
-        // launches after the (half) iteration at which a system converged are
-        // not counted for it
+        // launches queued after a system's loop had stopped did no work for it
         std::vector<StopPoint> stops;
         for (int k : act) {
             const SysState &st = *S_(R, k).st;
             const int ph = st.hf(L, F_STOPPH);
             if (st.hf(L, F_DONE) == DONE_NO || ph == 0) continue;
-            const int it = st.hf(L, F_ITERS);
-            stops.push_back(StopPoint{st.fl(L), ph == 1 ? it : it - 1, ph});
+            const int it = st.hf(L, F_ITERS), ran = st.hf(L, F_RAN);
+            if (R.pipe) stops.push_back(StopPoint{st.fl(L), ph == 1 ? it : it - 1, ph});
+            else stops.push_back(StopPoint{st.fl(L), it, ran == 2 ? 3 : ran});  // the update that stopped, or all of it
         }
         timing_settle(R.tl, timed_from, stops);
     }

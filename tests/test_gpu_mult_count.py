@@ -74,3 +74,26 @@ def test_mults_that_ran_in_the_pipelined_loop(every):
     rest = info["dslash_count"] - info["inner_calls"] * (4 + 4 * 5 + 2)
     assert rest == 5
     lat.close()
+
+
+@pytest.mark.parametrize("inner,name", [(wc.FP32, "fp32"), (wc.FP16, "fp16")])
+@pytest.mark.parametrize("every", [1, 500])
+def test_kernel_table_has_the_launches_that_ran(inner, name, every):
+    dims = (8, 8, 8, 8)
+    lat = wc.Lattice(dims)
+    lat.load_links(dev(synth.random_links(dims, 0.3, 1970)))
+    seen = set()
+    for seed in range(4):
+        b = dev(synth.gaussian_source(dims, 2970 + seed))
+        lat.solve(b, 0.13, 1.0, 1e-10, inner_prec=inner, check_every=every)
+        lat.reset_kernel_stats()
+        lat.set_timing(True)
+        _, info = lat.solve(b, 0.13, 1.0, 1e-10, inner_prec=inner, check_every=every)
+        lat.set_timing(False)
+        st = lat.kernel_stats()
+        hop, dh = st["mult_hopinv_" + name]["launches"], st["mult_dhat_" + name]["launches"]
+        say(info, hop, dh)
+        assert hop == dh and hop + dh == info["dslash_count"] - 5 - 2 * info["inner_calls"]
+        seen.add(hop + dh - 4 * info["inner_iters_total"])
+    assert seen == {0} if every == 1 else max(seen) > 0
+    lat.close()
