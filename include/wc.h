@@ -217,7 +217,9 @@ int wc_xcd_chunk(const wc_lattice *lat, int prec);
    D-hat half, and every other stencil) by the launch-shape tuner
    (wc_tune_block_size) among no cap, 8 and 12 waves; before tuning it is 8
    for FP64 and none for FP32 and FP16, and where the stencil gives each tile
-   four wavefronts (wc_set_block_size) it stays so.
+   four wavefronts (wc_set_block_size) it stays so.  In FP64 that stencil's own
+   LDS leaves room for 8 waves per compute unit, so there a cap of 0, 12 or 16 is
+   no different from 8.
    wc_set_wave_cap: 4, 8, 12 or 16 waves pins the cap of both classes, 0 pins
    no cap, -1 returns to tuning.  Changing it drops the tuned launch shape of
    that precision.  WC_EINVAL for other values or a bad precision.  Batches of

@@ -1160,10 +1160,11 @@ template <int P> void dispatch_mrhs(const MrhsArgs &A, int mode, int red, hipStr
 // small enough that every workgroup is resident at once.  Each phase of an
 // iteration ends in a grid-wide barrier instead of a kernel boundary; every
 // block then sums the reduction partials itself, all in one order, so all
-// blocks take the same decisions and leave the loop together.  The per-site arithmetic is that of
-// the stencil and vector kernels, and the scalars and flags are left exactly
-// as the launched path leaves them, so the host finishes the call the same
-// way.  Partials alternate between two buffers: a buffer is written again
+// blocks take the same decisions and leave the loop together.  It sums rho =
+// <r~, r> where the launched loop forms it from <r~, s> and <r~, t>, and notices
+// each stop at once; the per-site arithmetic is the same otherwise.  The flags, and
+// the scalars that the host's closing update reads, are left as the launched loop
+// leaves them, so the host finishes the call the same way.  Partials alternate between two buffers: a buffer is written again
 // only after a barrier that follows its last read.
 // ---------------------------------------------------------------------------
 struct PersistArgs {
@@ -1291,8 +1292,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(P == P64
     using R = typename Real<P>::T;
     constexpr int XP = P == P64 ? P64 : P32;
     using RX = typename Real<XP>::T;
-    enum { K_RQ = 0, K_SS = 2, K_ST = 3, K_TT = 5, K_RR = 6, K_N = 7 };
-    __shared__ double kept[K_N];  // last values, for the write-out by block 0
+    enum { K_RQ = 0, K_N = 2 };
+    __shared__ double kept[K_N];  // last <r~, q>, for the write-out by block 0
     const int Vh = A.g.Vh;
     const int lb = xcd_block(blockIdx.x, gridDim.x);  // neighbouring sites share an XCD's L2
     const int i = lb * kBlock + threadIdx.x;
@@ -1380,7 +1381,6 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(P == P64
             if (threadIdx.x == 0) {
                 kept[K_RQ] = rq.re;
                 kept[K_RQ + 1] = rq.im;
-                kept[K_SS] = n[0];
             }
             if (!(isfinite(al.re) && isfinite(al.im)) || !isfinite(n[0])) {
                 done = DONE_BREAK;
@@ -1434,12 +1434,6 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(P == P64
         sum_partials<3, 0>(SumSource{A.part[1], A.nblk}, SumSource{nullptr, 0}, v3);
         const double rr = v3[0];
         const cx<double> rho1 = {v3[1], v3[2]};
-        if (threadIdx.x == 0) {
-            kept[K_ST] = st.re;
-            kept[K_ST + 1] = st.im;
-            kept[K_TT] = tt;
-            kept[K_RR] = rr;
-        }
         const bool bad = !(tt > 0.0) || !(isfinite(om.re) && isfinite(om.im)) || !isfinite(rr) ||
                          (rho1.re == 0.0 && rho1.im == 0.0);
         if (bad || rr < tol2) {
@@ -1478,11 +1472,6 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(P == P64
         sc[S_RHO1 + 1] = rho.im;
         sc[S_RQ] = kept[K_RQ];
         sc[S_RQ + 1] = kept[K_RQ + 1];
-        sc[S_SS] = kept[K_SS];
-        sc[S_ST] = kept[K_ST];
-        sc[S_ST + 1] = kept[K_ST + 1];
-        sc[S_TT] = kept[K_TT];
-        sc[S_RR] = kept[K_RR];
         A.fl[F_DONE] = done;
         A.fl[F_ITERS] = it;
         A.fl[F_STOPPH] = stopph;

@@ -108,7 +108,7 @@ struct TimedLaunch {
 // One linear system's device-side solver state: scalar and flag blocks per
 // level, reduction partials, and pinned host mirrors.  The scalars and flags
 // of the systems of one solve sit in one contiguous arena so that a single
-// copy brings all of them to the host.
+// kernel (launch_publish) brings all of them to the host.
 struct SysState {
     double *scalars = nullptr;     // [NUM_LEVELS][S_COUNT]
     int *flags = nullptr;          // [NUM_LEVELS][F_COUNT]

@@ -6,7 +6,7 @@
 // Several systems (several sources on one lattice, or lattices of different
 // sizes) run in lockstep: every phase is one batched launch over the systems
 // that are still iterating, each system keeps its own scalars and done flag,
-// and one copy of the scalar arena per check serves all of them.
+// and one kernel per check brings the scalars and flags of all of them to the host.
 //
 // Readings of the printed algorithms (both listings agree on them):
 //   alpha = rho0 / <r~|q>             (the listings omit "rho0 /")
