@@ -404,7 +404,8 @@ inline unsigned cap_lds_bytes(const wc_lattice *lat, int prec, int bs, int mode 
 // Whether one-system stencils on lat in precision prec run with a tile's four
 // directions on four wavefronts (k_mult_split in dslash.hip) rather than one
 // thread per site.  FP64 and the FP32 two-column and full links always do: it
-// is faster at every size measured (8^4 to 48^3x96).  FP16 storage and
+// is faster at every size measured (8^4 to 48^3x96; least in FP64 at 32^3x64: MULT
+// 352.8 -> 348.0 us, D-hat_ee 749 -> 744).  FP16 storage and
 // reconstruct-8 links spend more of their time in arithmetic, and while two
 // wavefronts finish a tile the other two have none: they take it up to four tiles per
 // compute unit, where latency decides (D-hat_ee in FP16: 16^4 18.5 -> 14.6 us, 16^3x32
